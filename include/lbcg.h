@@ -137,9 +137,13 @@ typedef struct lbcg_fields {
  * T(zc) tiles of all cases and S workgroup slots for the fused kernel the
  * handle runs (CUs x the workgroups per CU that its registers and LDS allow,
  * queried from the runtime at init; a failed query is LBCG_EDEVICE), the
- * chunk in 8 .. 128 planes (FP32) or 8 .. 64 (16-bit forms) that minimises
+ * chunk in 1 .. 128 planes (FP32) or 1 .. 64 (16-bit forms) that minimises
  * ceil(T / S) (zc + 2), the longer on a tie, or the longest where that one
- * gives T >= 2 S; lbcg_zchunk reports it).
+ * gives T >= 2 S; lbcg_zchunk reports it).  Small boxes: where zchunk is 0 and
+ * all cases together are at most two 16 x 4 x 4 bricks per CU, the single-pass
+ * step advances bricks (zchunk 4) instead of marching tiles; so does a handle
+ * whose walls on x or y make LBCG_KERNEL_AUTO take the two-pass step, if
+ * block_nodes and persistent_blocks are 0 too.  The results agree to rounding.
  * graph_steps: 0 = launch every kernel of every step; n > 0 = capture n steps
  * (rounded up to even) once into a HIP graph and replay it; with diag_every
  * the stability check then runs at the first replay boundary at or after each
@@ -237,7 +241,7 @@ int lbcg_get_populations(lbcg_handle *h, int32_t case_id, float *f);
  * recording an event pair around every kernel of every following step
  * (enable = 0 stops).  lbcg_timing_read synchronises the stream and writes,
  * for the kernels {moments pass, wall ghost layer, collision pass, fused
- * step} (a handle on the fused step records only the last), the summed duration in milliseconds into ms[4] and the number of
+ * step} (a handle on the fused step, or on bricks, records only the last), the summed duration in milliseconds into ms[4] and the number of
  * recorded launches into launches[4]; it then clears the totals.  Errors: LBCG_ESTATE,
  * LBCG_EINVAL (NULL output), LBCG_EDEVICE. */
 int lbcg_timing(lbcg_handle *h, int32_t enable);

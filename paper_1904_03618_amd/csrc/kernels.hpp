@@ -284,7 +284,7 @@ __device__ inline void pull_issue(const StepArgs &a, DC &C, const Coord &c, type
 
 // Decode phase: deviations plus the writers' densities from the LDS plane
 // ring (as pull_one does with the densities from memory).
-template <int ST, bool MV, int I = 0>
+template <int ST, bool MV, int ROW = RW, int I = 0>
 __device__ inline void pull_decode(const StepArgs &a, DC &C, const Coord &c, const float2 own,
                                    const float2 *const (&rl)[3], int ri, const typename Storage<ST>::P (&v)[Q],
                                    NodeState &s, float &eR, float &eB)
@@ -294,7 +294,7 @@ __device__ inline void pull_decode(const StepArgs &a, DC &C, const Coord &c, con
         const bool bb = bounce<I>(c);
         const float dR = S::dec(v[I].r, a.inv_scale);
         const float dB = S::dec(v[I].b, a.inv_scale);
-        const float2 pl = rl[1 - ez(I)][ri - ex(I) - RW * ey(I)];
+        const float2 pl = rl[1 - ez(I)][ri - ex(I) - ROW * ey(I)];
         const float2 ps = bb ? own : pl;
         float tR = __builtin_fmaf(ps.x - own.x, C.phi[0][ecls(I)], dR);
         float tB = __builtin_fmaf(ps.y - own.y, C.phi[1][ecls(I)], dB);
@@ -315,20 +315,20 @@ __device__ inline void pull_decode(const StepArgs &a, DC &C, const Coord &c, con
         if constexpr (ey(I) == -1) s.jy -= h;
         if constexpr (ez(I) == 1) s.jz += h;
         if constexpr (ez(I) == -1) s.jz -= h;
-        pull_decode<ST, MV, I + 1>(a, C, c, own, rl, ri, v, s, eR, eB);
+        pull_decode<ST, MV, ROW, I + 1>(a, C, c, own, rl, ri, v, s, eR, eB);
     }
 }
 
 // The node state from the loaded populations of node c (ri: its index in
-// the density planes).
-template <int ST, bool MV>
+// the density planes, whose rows are ROW entries long).
+template <int ST, bool MV, int ROW = RW>
 __device__ inline void pull_finish(const StepArgs &a, DC &C, const Coord &c, const float2 *const (&rl)[3], int ri,
                                    const typename Storage<ST>::P (&v)[Q], NodeState &s)
 {
     const float2 own = rl[1][ri];
     float eR = 0.f, eB = 0.f;
     s.jx = s.jy = s.jz = 0.f;
-    pull_decode<ST, MV>(a, C, c, own, rl, ri, v, s, eR, eB);
+    pull_decode<ST, MV, ROW>(a, C, c, own, rl, ri, v, s, eR, eB);
     s.R[0] = own.x + eR;
     s.R[1] = own.y + eB;
     s.D[0] = s.R[0] - own.x;
@@ -441,7 +441,7 @@ struct WriterRing {
     const float *c[3];
 };
 
-template <int ST, bool MV, int I = 1>
+template <int ST, bool MV, int ROW = RW, int I = 1>
 __device__ inline void pull_decode_c(const StepArgs &a, DC &C, const Coord &c, const float2 own,
                                      const WriterRing &wr, int ri, const CompactPull<ST> &p, NodeState &s,
                                      float &eR, float &eB)
@@ -449,12 +449,12 @@ __device__ inline void pull_decode_c(const StepArgs &a, DC &C, const Coord &c, c
     if constexpr (I < Q) {
         using S = Storage<ST>;
         const bool bb = bounce<I>(c);
-        const int li = bb ? ri : ri - ex(I) - RW * ey(I);
+        const int li = bb ? ri : ri - ex(I) - ROW * ey(I);
         const float2 *R = bb ? wr.r[1] : wr.r[1 - ez(I)];
         const float4 *D = bb ? wr.d[1] : wr.d[1 - ez(I)];
         const float *Cw = bb ? wr.c[1] : wr.c[1 - ez(I)];
         decode_c<ST, MV, I>(C, c, own, bb, S::dec(p.v[I], a.inv_scale), R[li], D[li], Cw[li], s, eR, eB);
-        pull_decode_c<ST, MV, I + 1>(a, C, c, own, wr, ri, p, s, eR, eB);
+        pull_decode_c<ST, MV, ROW, I + 1>(a, C, c, own, wr, ri, p, s, eR, eB);
     }
 }
 
@@ -480,7 +480,7 @@ __device__ inline void finish_state(const float2 own, float eR, float eB, NodeSt
 }
 
 // The node state from a compact pull, writers' data from the LDS rings.
-template <int ST, bool MV>
+template <int ST, bool MV, int ROW = RW>
 __device__ inline void pull_finish_c(const StepArgs &a, DC &C, const Coord &c, const WriterRing &wr, int ri,
                                      const CompactPull<ST> &p, NodeState &s)
 {
@@ -488,7 +488,7 @@ __device__ inline void pull_finish_c(const StepArgs &a, DC &C, const Coord &c, c
     float eR, eB;
     s.jx = s.jy = s.jz = 0.f;
     own_pair<ST>(a, p.v0, s, eR, eB);
-    pull_decode_c<ST, MV>(a, C, c, own, wr, ri, p, s, eR, eB);
+    pull_decode_c<ST, MV, ROW>(a, C, c, own, wr, ri, p, s, eR, eB);
     finish_state(own, eR, eB, s);
 }
 
@@ -1040,12 +1040,12 @@ __device__ inline void fpull_issue(const StepArgs &a, DC &C, const Coord &c, FPu
     else pull_issue<ST, CPP, SO>(a, C, c, p.v);
 }
 
-template <int ST, int IN, bool MV>
+template <int ST, int IN, bool MV, int ROW = RW>
 __device__ inline void fpull_finish(const StepArgs &a, DC &C, const Coord &c, const WriterRing &wr, int ri,
                                     const FPull<ST, IN> &p, NodeState &s)
 {
-    if constexpr (IN == LV_COMPACT) pull_finish_c<ST, MV>(a, C, c, wr, ri, p, s);
-    else pull_finish<ST, MV>(a, C, c, wr.r, ri, p.v, s);
+    if constexpr (IN == LV_COMPACT) pull_finish_c<ST, MV, ROW>(a, C, c, wr, ri, p, s);
+    else pull_finish<ST, MV, ROW>(a, C, c, wr.r, ri, p.v, s);
 }
 
 // Position (relative to the tile origin) of entry e of the halo of width h
@@ -1325,6 +1325,220 @@ __global__ __launch_bounds__(FNT) void k_fused(FusedArgs fa)
                                                                                ring[fslot(z)][fidx(tx, ty)].x);
             }
             cur = nxt;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- k_brick
+// Single-pass step for boxes too small to fill the GPU with k_fused's
+// marching tiles (whose planes follow each other, about 5 us each with one
+// workgroup on a CU).  A workgroup owns a KX x KY x KZ brick of nodes and does
+// everything at once: every node of the brick and of its one-node halo has a
+// lane of its own (256 + 392), so the step is one memory latency, one pull, one
+// barrier and one collision long whatever the box.  It pulls 2.5 nodes per
+// node it advances, which is why larger boxes march instead.  The writers' words
+// of the brick plus two nodes on each side are staged in LDS, as are the aux
+// values; walls on any axis (WL): the ghost layer is computed in LDS from the
+// first layer, whose phase field two nodes around the brick the remaining lanes
+// pull with the writers' words read from memory.
+constexpr int KX = 16, KY = 4, KZ = 4;
+constexpr int KOWN = KX * KY * KZ;
+constexpr int KHALO = (KX + 2) * (KY + 2) * (KZ + 2) - KOWN;
+constexpr int KNT = 704;                               // lanes: own, halo, and 56 for a wall's outer ring
+constexpr int KRX = KX + 4, KRY = KY + 4, KPL = KRX * KRY, KREG = KPL * (KZ + 4);
+static_assert(KOWN == 256 && KOWN + KHALO < KNT && KREG <= 2 * KNT, "lane roles of the brick kernel");
+
+__device__ inline int kidx(int rx, int ry, int rz) { return (rx + 2) + KRX * (ry + 2) + KPL * (rz + 2); }
+
+// Position (relative to the brick origin) of halo entry e: the planes below and
+// above, then the ring around each of the brick's own planes.
+__device__ inline void brick_halo_pos(int e, int &rx, int &ry, int &rz)
+{
+    constexpr int W = KX + 2, FACE = W * (KY + 2), RING = 2 * W + 2 * KY;
+    if (e < 2 * FACE) {
+        const int r = e >= FACE ? e - FACE : e;
+        rz = e >= FACE ? KZ : -1;
+        ry = r / W - 1;
+        rx = r % W - 1;
+    } else {
+        const int e1 = e - 2 * FACE, r = e1 % RING;
+        rz = e1 / RING;
+        if (r < 2 * W) {
+            ry = r < W ? -1 : KY;
+            rx = (r < W ? r : r - W) - 1;
+        } else {
+            ry = (r - 2 * W) >> 1;
+            rx = ((r - 2 * W) & 1) ? KX : -1;
+        }
+    }
+}
+
+template <int I = 1>
+__device__ inline void stencil_brick(const float4 *aux, int i, Stencil &st)
+{
+    if constexpr (I < Q) {
+        constexpr int X = ex(I), Y = ey(I), Z = ez(I);
+        constexpr float w3 = ecls(I) == 1 ? (1.0f / 6.0f) : (1.0f / 12.0f);
+        const float4 v = aux[i + X + KRX * Y + KPL * Z];
+        if constexpr (X != 0) { st.gx += (X * w3) * v.x; st.Qx += (X * w3) * v.y; }
+        if constexpr (Y != 0) { st.gy += (Y * w3) * v.x; st.Qy += (Y * w3) * v.z; }
+        if constexpr (Z != 0) { st.gz += (Z * w3) * v.x; st.Qz += (Z * w3) * v.w; }
+        stencil_brick<I + 1>(aux, i, st);
+    }
+}
+
+// Levels are read through one buffer resource per case (the host takes this
+// kernel only where every case's level allows it).
+template <int ST, bool MV, int WL, int IN, int OUT>
+__global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
+{
+    __shared__ float4 aux[KREG];
+    __shared__ float2 rr[KREG];
+    __shared__ float4 dd[IN == LV_COMPACT ? KREG : 1];
+    __shared__ float cc[IN == LV_COMPACT ? KREG : 1];
+    __shared__ float wq[MV ? KREG : 1];                // density factor of Qbar (moving walls)
+    const StepArgs &a = fa.a;
+    const TileRange tr = tile_range(fa.nftiles);
+    const int tid = (int)threadIdx.x;
+    // this lane's position in the brick: own nodes first, then the halo
+    int px = tid % KX, py = (tid / KX) % KY, pz = tid / (KX * KY);
+    if (tid >= KOWN) brick_halo_pos(min(tid - KOWN, KHALO - 1), px, py, pz);
+    for (int t = tr.first; t < tr.end; t += tr.stride) {
+        const int4 tl = fa.ftiles[t];
+        DC &C = case_at(a.cases, tl.x);
+        const int x0 = tl.y, y0 = tl.z, z0 = tl.w;
+        const int ax = min(KX, C.nx - x0), ay = min(KY, C.ny - y0), az = min(KZ, C.nz - z0);
+        // a coordinate beyond a wall (never wrapped); the others wrap
+        auto beyond = [&](int x, int y, int z) {
+            if (WL == WALLS_NONE) return false;
+            if (WL == WALLS_Z) return C.wall == 2 && (z < 0 || z >= C.nz);
+            return (C.wall == 0 && (x < 0 || x >= C.nx)) || (C.wall == 1 && (y < 0 || y >= C.ny)) ||
+                   (C.wall == 2 && (z < 0 || z >= C.nz));
+        };
+        auto wrap = [](int v, int n) { return (v + 4 * n) % n; };       // v >= -2 >= -2 n
+        // a ragged brick's upper halo falls on lanes of the full brick's own nodes
+        const bool own = tid < KOWN && px < ax && py < ay && pz < az;
+        const bool pull = tid < KOWN + KHALO && px <= ax && py <= ay && pz <= az &&
+                          !beyond(x0 + px, y0 + py, z0 + pz);
+        const Coord c = make_coord_xyz<WL>(C, wrap(x0 + px, C.nx), wrap(y0 + py, C.ny), wrap(z0 + pz, C.nz));
+        FPull<ST, IN> v;
+        if (pull) fpull_issue<ST, IN, CP_DEFAULT, true>(a, C, c, v);
+        // the writers' words of the brick and two nodes around it, two entries
+        // per lane; positions outside load node 0 and are not stored
+        auto stage_at = [&](int e, bool &ok) {
+            const int rx = e % KRX - 2, ry = (e / KRX) % KRY - 2, rz = e / KPL - 2;
+            ok = e < KREG && rx <= ax + 1 && ry <= ay + 1 && rz <= az + 1 && !beyond(x0 + rx, y0 + ry, z0 + rz);
+            return (size_t)C.node_off +
+                   (ok ? wrap(x0 + rx, C.nx) + C.nx * (wrap(y0 + ry, C.ny) + C.ny * wrap(z0 + rz, C.nz)) : 0);
+        };
+        bool ok0, ok1;
+        const size_t g0 = stage_at(tid, ok0), g1 = stage_at(tid + KNT, ok1);
+        const float2 r0 = a.rho_prev[g0], r1 = a.rho_prev[g1];
+        float4 d0, d1;
+        float c0, c1;
+        if constexpr (IN == LV_COMPACT) {
+            d0 = a.dsc_prev[g0];
+            d1 = a.dsc_prev[g1];
+            c0 = a.crs_prev[g0];
+            c1 = a.crs_prev[g1];
+        }
+        __syncthreads();                               // the previous brick's collisions have read the LDS arrays
+        if (ok0) {
+            rr[tid] = r0;
+            if constexpr (IN == LV_COMPACT) {
+                dd[tid] = d0;
+                cc[tid] = c0;
+            }
+        }
+        if (ok1) {
+            rr[tid + KNT] = r1;
+            if constexpr (IN == LV_COMPACT) {
+                dd[tid + KNT] = d1;
+                cc[tid + KNT] = c1;
+            }
+        }
+        __syncthreads();
+        NodeState s;
+        if (pull) {
+            WriterRing wr;
+            #pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const int pl = KPL * (pz + 1 + k);
+                wr.r[k] = rr + pl;
+                wr.d[k] = dd + (IN == LV_COMPACT ? pl : 0);
+                wr.c[k] = cc + (IN == LV_COMPACT ? pl : 0);
+            }
+            fpull_finish<ST, IN, MV, KRX>(a, C, c, wr, (px + 2) + KRX * (py + 2), v, s);
+            float qs;
+            aux[kidx(px, py, pz)] = aux_value(C, s, qs);
+            if (MV) wq[kidx(px, py, pz)] = qs;
+        }
+        if constexpr (WL != WALLS_NONE) {
+            // wall bricks: sides s0 .. s1 - 1 (0 low, 1 high) touch the brick;
+            // (b, w) of a position: in-plane coordinates and the wall coordinate
+            const int w = WL == WALLS_Z ? 2 : C.wall;
+            const int o0 = w == 0 ? x0 : (w == 1 ? y0 : z0), aw = w == 0 ? ax : (w == 1 ? ay : az);
+            const int nw = w == 0 ? C.nx : (w == 1 ? C.ny : C.nz);
+            const bool has = WL == WALLS_Z ? C.wall == 2 : C.wall >= 0;
+            const int s0 = has && o0 == 0 ? 0 : 1, s1 = has && o0 + aw == nw ? 2 : 1;
+            const int ab = w == 0 ? ay : ax, ac = w == 2 ? ay : az;      // in-plane extents
+            auto at = [&](int b, int cax, int layer, int &rx, int &ry, int &rz) {
+                rx = w == 0 ? layer : b;
+                ry = w == 0 ? b : (w == 1 ? layer : cax);
+                rz = w == 2 ? layer : cax;
+            };
+            if (s0 < s1) {
+                const int n = 2 * (ab + 4) + 2 * (ac + 2);               // the ring at distance 2
+                for (int q = tid - (KOWN + KHALO); q < n * (s1 - s0); q += KNT - (KOWN + KHALO)) {
+                    if (q < 0) break;
+                    const int k = q >= n;
+                    int b, cax, rx, ry, rz;
+                    ring2_pos(q - k * n, ab, ac, b, cax);
+                    at(b, cax, (s0 + k ? nw - 1 : 0) - o0, rx, ry, rz);
+                    const Coord ch = make_coord_xyz<WL>(C, wrap(x0 + rx, C.nx), wrap(y0 + ry, C.ny),
+                                                        wrap(z0 + rz, C.nz));
+                    NodeState hs;
+                    if constexpr (IN == LV_COMPACT) pull_node_c<ST, MV>(a, C, ch, hs);
+                    else pull_node<ST, MV, CP_DEFAULT>(a, C, ch, hs);
+                    float qs;
+                    aux[kidx(rx, ry, rz)] = aux_value(C, hs, qs);
+                    if (MV) wq[kidx(rx, ry, rz)] = qs;
+                }
+                __syncthreads();
+                const int wb = ab + 2, ng = wb * (ac + 2);
+                const int sb = w == 0 ? KRX : 1, scx = w == 2 ? KRX : KPL, sw = w == 0 ? 1 : (w == 1 ? KRX : KPL);
+                for (int q = tid; q < ng * (s1 - s0); q += KNT) {
+                    const int side = s0 + (q >= ng), r = q >= ng ? q - ng : q;
+                    int rx, ry, rz;
+                    at(r % wb - 1, r / wb - 1, (side ? nw - 1 : 0) - o0, rx, ry, rz);
+                    const int i = kidx(rx, ry, rz);
+                    float gb = 0.f, gc = 0.f;
+                    #pragma unroll
+                    for (int db = -1; db <= 1; ++db) {
+                        #pragma unroll
+                        for (int dc = -1; dc <= 1; ++dc) {
+                            if (db == 0 && dc == 0) continue;
+                            const float wgt = (db != 0 && dc != 0) ? (1.0f / 12.0f) : (1.0f / 3.0f);
+                            const float u = aux[i + db * sb + dc * scx].x;
+                            gb += wgt * (float)db * u;
+                            gc += wgt * (float)dc * u;
+                        }
+                    }
+                    const float4 f = aux[i];
+                    const float gpar = sqrtf(gb * gb + gc * gc);
+                    const float qw = MV && C.moving ? 2.0f * wq[i] : 0.f;
+                    aux[side ? i + sw : i - sw] =
+                        make_float4(f.x + C.cot[side] * gpar, qw * C.uw[side][0] - f.y, qw * C.uw[side][1] - f.z,
+                                    qw * C.uw[side][2] - f.w);
+                }
+            }
+        }
+        __syncthreads();
+        if (own) {
+            const int i = kidx(px, py, pz);
+            Stencil st = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            stencil_brick(aux, i, st);
+            collide_node<ST, CP_DEFAULT, OUT>(a, C, c.node, s, st, aux[i].x);
         }
     }
 }

@@ -76,6 +76,7 @@ struct lbcg_handle {
     int64_t launches[4] = {0, 0, 0, 0};
     // fused single-pass step
     bool fused = false;
+    bool brick = false;                // small boxes: k_brick instead of k_fused or the two-pass kernels
     int zc = 16;
     int4 *d_ftiles = nullptr;
     int nftiles = 0;
@@ -321,22 +322,54 @@ int fused_blocks_per_cu(const lbcg_handle *h)
     }
 }
 
+template <int ST, int IN, int OUT>
+void launch_brick(lbcg_handle *h, hipStream_t st, const FusedArgs &fa, int grid)
+{
+    const dim3 g(grid), b(KNT);
+    if constexpr (IN == LV_PAIR && OUT == LV_PAIR) {   // walls on x or y: pair levels only
+        if (h->walls == WALLS_ANY) {
+            if (h->moving) hipLaunchKernelGGL((k_brick<ST, true, WALLS_ANY, IN, OUT>), g, b, 0, st, fa);
+            else hipLaunchKernelGGL((k_brick<ST, false, WALLS_ANY, IN, OUT>), g, b, 0, st, fa);
+            return;
+        }
+    }
+    if (h->moving) hipLaunchKernelGGL((k_brick<ST, true, WALLS_Z, IN, OUT>), g, b, 0, st, fa);
+    else if (h->walls == WALLS_Z) hipLaunchKernelGGL((k_brick<ST, false, WALLS_Z, IN, OUT>), g, b, 0, st, fa);
+    else hipLaunchKernelGGL((k_brick<ST, false, WALLS_NONE, IN, OUT>), g, b, 0, st, fa);
+}
+
+// The single-pass step (marching tiles or bricks) of a run of cases whose
+// levels are read in the format fmt.
+template <int ST>
+void launch_single_pass(lbcg_handle *h, hipStream_t st, const FusedArgs &fa, int grid, int fmt)
+{
+    if (h->brick) {
+        // the 16-bit forms take bricks with pair levels only (the host's rule)
+        if constexpr (ST == LBCG_FP32) {
+            if (h->level == LV_COMPACT) {
+                if (fmt == LV_PAIR) launch_brick<ST, LV_PAIR, LV_COMPACT>(h, st, fa, grid);
+                else launch_brick<ST, LV_COMPACT, LV_COMPACT>(h, st, fa, grid);
+                return;
+            }
+        }
+        launch_brick<ST, LV_PAIR, LV_PAIR>(h, st, fa, grid);
+    } else if (h->level == LV_PAIR) launch_fused<ST, LV_PAIR, LV_PAIR>(h, st, fa, grid);
+    else if (fmt == LV_PAIR) launch_fused<ST, LV_PAIR, LV_COMPACT>(h, st, fa, grid);
+    else launch_fused<ST, LV_COMPACT, LV_COMPACT>(h, st, fa, grid);
+}
+
 template <int ST>
 int launch_step(lbcg_handle *h, hipStream_t st)
 {
     StepArgs a = args_for(h);
-    if (h->fused) {
+    if (h->fused || h->brick) {
         int rc = for_format_runs(h, [&](int fmt, int c0, int c1) {
             const int t0 = h->ftile_begin[c0];
             const int nt = h->ftile_begin[c1 - 1] + h->ftile_count[c1 - 1] - t0;
             if (nt <= 0) return (int)LBCG_OK;
             FusedArgs fa{a, h->d_ftiles + t0, nt, h->zc};
             const int grid = h->persistent > 0 ? h->persistent : nt;
-            return timed(h, 3, [&] {
-                if (h->level == LV_PAIR) launch_fused<ST, LV_PAIR, LV_PAIR>(h, st, fa, grid);
-                else if (fmt == LV_PAIR) launch_fused<ST, LV_PAIR, LV_COMPACT>(h, st, fa, grid);
-                else launch_fused<ST, LV_COMPACT, LV_COMPACT>(h, st, fa, grid);
-            });
+            return timed(h, 3, [&] { launch_single_pass<ST>(h, st, fa, grid, fmt); });
         });
         if (rc) return rc;
         HIPCHK(hipGetLastError());
@@ -606,7 +639,7 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     if (!out) return fail(LBCG_EINVAL, "out is NULL");
     *out = nullptr;
     if (!cases || !init || n_cases < 1) return fail(LBCG_EINVAL, "cases/init NULL or n_cases < 1");
-    lbcg_options o = {LBCG_FP32, 0, 256, 0, LBCG_KERNEL_AUTO, 0, 0, 0};
+    lbcg_options o = {LBCG_FP32, 0, 0, 0, LBCG_KERNEL_AUTO, 0, 0, 0};
     if (opt) o = *opt;
     if (o.graph_steps < 0) return fail(LBCG_EINVAL, "graph_steps must be >= 0");
     if (o.kernel < LBCG_KERNEL_AUTO || o.kernel > LBCG_KERNEL_FUSED) return fail(LBCG_EINVAL, "unknown kernel");
@@ -614,6 +647,7 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     if (o.level < LBCG_LEVEL_AUTO || o.level > LBCG_LEVEL_COMPACT) return fail(LBCG_EINVAL, "unknown level format");
     if (o.storage != LBCG_FP32 && o.storage != LBCG_FP16S && o.storage != LBCG_BF16S)
         return fail(LBCG_EINVAL, "unknown storage format");
+    const int opt_block = o.block_nodes;
     if (o.block_nodes == 0) o.block_nodes = 256;
     if (o.block_nodes < 64 || o.block_nodes > 256 || o.block_nodes % 64)
         return fail(LBCG_EINVAL, "block_nodes must be 64, 128, 192 or 256");
@@ -687,39 +721,56 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
         if ((int64_t)38 * d.NS * elem >= lim) h->one_rsrc[LV_PAIR] = false;
         if ((int64_t)20 * d.NS * elem >= lim) h->one_rsrc[LV_COMPACT] = false;
     }
+    int dev = 0, ncu = 0;
+    const bool dev_ok = hipGetDevice(&dev) == hipSuccess &&
+                        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0;
+    auto ntiles_of = [&](int tx, int ty, int tz) {
+        int64_t n = 0;
+        for (const DevCase &d : h->dc)
+            n += (int64_t)((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) * ((d.nz + tz - 1) / tz);
+        return n;
+    };
+    // Small boxes take the brick kernel where the caller left the launch shape
+    // open: up to two bricks per CU.  A round of bricks takes about 10 us
+    // whatever the box, a marching tile 3 + 5 (zc + 2) us at its best chunk
+    // below, and the two-pass step 13 us plus its bandwidth.  Measured, FP32 us
+    // per step, brick / marching (best chunk) / two-pass: 32^3 (128 bricks)
+    // 12.0 / 19.8 / 13.9, 32 x 32 x 128 (512) 21.1 / 24.4 / 19.3, 48^3 (432)
+    // 23.5 / 29.0 / 19.0, 64^3 (1024) 43.0 / 32.3 / 34.0; FP16S at 48^3 23.0 /
+    // 24.6, at 64^3 41.9 / 28.5.  A handle that has to take the two-pass step
+    // (walls on x or y, pair levels) saves two launches; the moving plates
+    // on 140 x 140 x 4 nodes (315 bricks) 40 -> 23.
+    const bool shape_open = o.zchunk == 0 && (h->fused || (o.kernel == LBCG_KERNEL_AUTO && opt_block == 0 &&
+                                                          o.persistent_blocks == 0));
+    h->brick = dev_ok && shape_open && h->one_rsrc[h->level] && (h->level == LV_PAIR || o.storage == LBCG_FP32) &&
+               ntiles_of(KX, KY, KZ) <= 2 * (int64_t)ncu;
     h->zc = o.zchunk;
-    if (h->zc == 0 && h->fused) {
+    if (h->brick) {
+        h->zc = KZ;
+    } else if (h->zc == 0 && h->fused) {
         // default chunk: a workgroup's tile of zc planes pulls zc + 2 planes,
         // and a launch of T tiles on S workgroup slots (CUs x workgroups of
         // this kernel per CU) takes about ceil(T / S) such tiles in turn, so
-        // the chunk (8 .. 128 planes for FP32, 8 .. 64 for the 16-bit forms)
+        // the chunk (1 .. 128 planes for FP32, 1 .. 64 for the 16-bit forms)
         // minimises ceil(T / S) (zc + 2), the longer chunk on a tie; where the
         // longest chunk already leaves two rounds or more it is taken.
         // Measured: 128 x 128 x 512 FP16S 43 planes (one tile per slot) 0.449
         // ms against 0.465 at 16; the 128^3 droplet FP16S 11 planes 0.1225
         // against 0.134; FP32 there 64 and 16, the 256 x 256 x 1024 box 128
-        // and 64, as before.
-        int dev = 0, ncu = 0;
+        // and 64, as before; 64^3 FP32 2 planes 32.3 us against 62.8 at 8 (128
+        // tiles on 512 slots), FP16S 28.5 against 53.2.
         const int nb = fused_blocks_per_cu(h);
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0 ||
-            nb <= 0) {
+        if (!dev_ok || nb <= 0) {
             delete h;
             return fail(LBCG_EDEVICE, "occupancy query of the fused kernel failed");
         }
         const int64_t slots = (int64_t)ncu * nb;
-        auto tiles = [&](int zc) {
-            int64_t n = 0;
-            for (const DevCase &d : h->dc)
-                n += (int64_t)((d.nx + FTX - 1) / FTX) * ((d.ny + FTY - 1) / FTY) * ((d.nz + zc - 1) / zc);
-            return n;
-        };
         const int cap = o.storage == LBCG_FP32 ? 128 : 64;
         h->zc = cap;
-        if (tiles(cap) < 2 * slots) {
+        if (ntiles_of(FTX, FTY, cap) < 2 * slots) {
             int64_t best = -1;
-            for (int zc = cap; zc >= 8; --zc) {
-                const int64_t cost = (tiles(zc) + slots - 1) / slots * (zc + 2);
+            for (int zc = cap; zc >= 1; --zc) {
+                const int64_t cost = (ntiles_of(FTX, FTY, zc) + slots - 1) / slots * (zc + 2);
                 if (best < 0 || cost < best) {
                     best = cost;
                     h->zc = zc;
@@ -734,10 +785,11 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     for (int c = 0; c < n_cases; ++c) {
         h->ftile_begin.push_back((int)ftiles.size());
         const DevCase &d = h->dc[c];
-        if (h->fused)
+        const int sx = h->brick ? KX : FTX, sy = h->brick ? KY : FTY;
+        if (h->fused || h->brick)
             for (int z0 = 0; z0 < d.nz; z0 += h->zc)
-                for (int y0 = 0; y0 < d.ny; y0 += FTY)
-                    for (int x0 = 0; x0 < d.nx; x0 += FTX) ftiles.push_back(make_int4(c, x0, y0, z0));
+                for (int y0 = 0; y0 < d.ny; y0 += sy)
+                    for (int x0 = 0; x0 < d.nx; x0 += sx) ftiles.push_back(make_int4(c, x0, y0, z0));
         h->ftile_count.push_back((int)ftiles.size() - h->ftile_begin.back());
     }
     h->nftiles = (int)ftiles.size();
