@@ -738,12 +738,17 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     // 12.0 / 19.8 / 13.9, 32 x 32 x 128 (512) 21.1 / 24.4 / 19.3, 48^3 (432)
     // 23.5 / 29.0 / 19.0, 64^3 (1024) 43.0 / 32.3 / 34.0; FP16S at 48^3 23.0 /
     // 24.6, at 64^3 41.9 / 28.5.  A handle that has to take the two-pass step
-    // (walls on x or y, pair levels) saves two launches; the moving plates
-    // on 140 x 140 x 4 nodes (315 bricks) 40 -> 23.
-    const bool shape_open = o.zchunk == 0 && (h->fused || (o.kernel == LBCG_KERNEL_AUTO && opt_block == 0 &&
-                                                          o.persistent_blocks == 0));
-    h->brick = dev_ok && shape_open && h->one_rsrc[h->level] && (h->level == LV_PAIR || o.storage == LBCG_FP32) &&
-               ntiles_of(KX, KY, KZ) <= 2 * (int64_t)ncu;
+    // (walls on x or y, pair levels) saves two launches with one brick per CU
+    // (13.9 + 4.6 us against 12), with moving walls, whose passes are longer, with
+    // two (the plates on 140 x 140 x 4 nodes, 315 bricks: 40 -> 22; at rest 42 x
+    // 69 x 20, 270 bricks, 18.7 against 25.5), in FP32: in the 16-bit forms the
+    // passes' last-bit rounding would change the stored values.
+    const int64_t bricks = ntiles_of(KX, KY, KZ);
+    const bool single = h->fused && bricks <= 2 * (int64_t)ncu;
+    const bool instead = !h->fused && o.kernel == LBCG_KERNEL_AUTO && opt_block == 0 && o.persistent_blocks == 0 &&
+                         o.storage == LBCG_FP32 && bricks <= (h->moving ? 2 : 1) * (int64_t)ncu;
+    h->brick = dev_ok && o.zchunk == 0 && (single || instead) && h->one_rsrc[h->level] &&
+               (h->level == LV_PAIR || o.storage == LBCG_FP32);
     h->zc = o.zchunk;
     if (h->brick) {
         h->zc = KZ;
