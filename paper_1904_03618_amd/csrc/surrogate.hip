@@ -163,20 +163,24 @@ __global__ __launch_bounds__(256) void k_conv_fwd(sg_view x, const bf16 *__restr
         }
 }
 
-// 3x3x3 convolution on a brick of 16 (x) x 4 (y) x 4 ZW (z) output positions of
-// one batch item, for tensors whose extents are multiples of the brick.  The
-// brick's input halo (18 x 6 x (4 ZW + 2) positions) is staged in LDS one chunk
-// of CT input channels at a time, so each input value is fetched from memory
-// once per chunk instead of once per tap; the 27 taps then read their B
-// fragments from LDS.  Wave w owns z-planes w ZW .. w ZW + ZW - 1 of the brick
-// (4 ZW rows of 16 positions) and NO blocks of 16 output channels.  Layers with
-// few input channels use ZW = 2, CT = 16: twice the MFMA work per staged halo at
-// the same LDS size.  A staged position holds CT/8 16-byte chunks; the chunk
-// index is XOR-swizzled with the position's x so that the 16 lanes of a
-// fragment read (consecutive x, one chunk each) cover 256 distinct bytes and
-// fall into different banks without padding.
-constexpr int BX = 16, BY = 4;
-constexpr int HX = BX + 2, HY = BY + 2;
+// 3x3x3 convolution on a brick of 16 (x) x 4 (y) x BZ (z) output positions of
+// one batch item, for tensors whose extents are multiples of 16, 4 and 4.  The
+// brick's input halo is staged in LDS one chunk of CT input channels at a time,
+// so each input value is fetched from memory once per chunk instead of once per
+// tap; the 27 taps then read their B fragments (a row of 16 positions) from LDS.
+// Wave w owns ZW = BZ / 4 z-planes of the brick and NO blocks of 16 output
+// channels.  A staged position holds CT/8 16-byte chunks, XOR-swizzled with the
+// position's x against bank conflicts.
+// DYR: the order in which a chunk's products are summed.  true: K blocks of four
+// (dz, dx, channel group) combinations, each block's three dy taps in turn; a
+// lane then loads the 6 halo rows its 4 output rows need once and feeds them to
+// three K blocks, half the LDS reads.  false: K blocks of four consecutive (tap,
+// channel group) pairs.  The order of a layer is fixed by its channels and
+// extents (sg_conv3d_fwd): networks reproduce their activations bit for bit
+// whatever brick or launch shape runs the layer.
+// WLDS: the chunk's weights are staged in LDS too, and the next chunk's loads
+// fly during the K loop.  For launches that leave CUs idle or with one workgroup:
+// there every K block would otherwise wait for its weights from L2.
 
 // Workgroups are dealt to the 8 XCDs in turn by their linear id (x
 // fastest).  This bijection on 0 .. n-1 maps the linear id to a position in
@@ -188,241 +192,415 @@ __device__ inline unsigned xcd_contiguous(unsigned lin, unsigned n)
     return x * q + min(x, r) + l;
 }
 
-template <int NO, int ZW, int CT, bool DYR>
-__global__ __launch_bounds__(256) void k_conv3_brick(sg_view x, const bf16 *__restrict__ W,
-                                                     const float *__restrict__ bias, int pmask, int relu, sg_view y,
-                                                     sg_view y32, int accumulate)
+// Coordinate g in -1 .. n of an axis of n positions: wrapped when periodic, -1
+// where the input is zero.
+__device__ inline int edge(int g, int n, bool periodic)
 {
-    constexpr int BZ = 4 * ZW, HZ = BZ + 2, HP = HX * HY * HZ, LROW = CT, NF = 4 * ZW;
+    if (g < 0) return periodic ? n - 1 : -1;
+    if (g < n) return g;
+    return periodic ? 0 : -1;
+}
+
+// A lane's 4 consecutive output channels oc0 .. of position pb, stored as one
+// 8-byte (BF16) or 16-byte (FP32) access when the slice allows it.
+__device__ inline void store_out(const sg_view &y, const sg_view &y32, int64_t pb, int oc0, f32x4 v, int relu,
+                                 int accumulate)
+{
+    if (relu)
+        #pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
+    if (y.p) {
+        bf16 *out = reinterpret_cast<bf16 *>(y.p) + pb * y.ctot + y.coff + oc0;
+        if (((y.ctot | y.coff) & 3) == 0 && oc0 + 3 < y.c) {
+            *reinterpret_cast<bf16x4 *>(out) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+        } else {
+            #pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (oc0 + j < y.c) out[j] = (bf16)v[j];
+        }
+    }
+    if (y32.p) {
+        float *out = reinterpret_cast<float *>(y32.p) + pb * y32.ctot + y32.coff + oc0;
+        if (((y32.ctot | y32.coff) & 3) == 0 && oc0 + 3 < y32.c) {
+            f32x4 *o4 = reinterpret_cast<f32x4 *>(out);
+            *o4 = accumulate ? *o4 + v : v;
+        } else {
+            #pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (oc0 + j < y32.c) out[j] = accumulate ? out[j] + v[j] : v[j];
+        }
+    }
+}
+
+// The biases of output channels oc0 .. oc0 + 3 (zero past the views' channels).
+__device__ inline f32x4 bias4(const float *bias, int oc0, const sg_view &y, const sg_view &y32)
+{
+    const int nb = max(y.p ? y.c : 0, y32.p ? y32.c : 0);
+    f32x4 b;
+    #pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = bias && oc0 + j < nb ? bias[oc0 + j] : 0.f;
+    return b;
+}
+
+template <int NO, int BZ, int CT, bool DYR, bool WLDS>
+__global__ __launch_bounds__(256) void k_conv3(sg_view x, const bf16 *__restrict__ W, const float *__restrict__ bias,
+                                               int pmask, int relu, sg_view y, sg_view y32, int accumulate, int nbx,
+                                               int nby, int nbz)
+{
+    constexpr int BX = 16, BY = 4, HX = BX + 2, HY = BY + 2, HZ = BZ + 2, ROWS = HY * HZ, HP = HX * ROWS;
     constexpr int NC = CT / 8, XSPAN = 16 / NC;           // chunks per position; positions per 256 bytes
-    auto swz = [](int hx, int c8) { return c8 ^ ((hx / XSPAN) & (NC - 1)); };
-    __shared__ __attribute__((aligned(16))) bf16 halo[HP * LROW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int ZW = BZ / 4, NF = ZW * BY, NR = BY + 2;
+    static_assert(BZ % 4 == 0 && ZW <= 2, "brick shape");
+    // staging: rows of BX interior positions, RPW rows per wave and load, then
+    // the two side columns of every row
+    constexpr int LR = BX * NC, RPW = 64 / LR, NL = (ROWS + 4 * RPW - 1) / (4 * RPW);
+    constexpr int SIDE = 2 * NC * ROWS, NS = (SIDE + 255) / 256;
+    constexpr int WE = WLDS ? 27 * 16 * NO * NC : 0, NW = (WE + 255) / 256;
+    __shared__ __attribute__((aligned(16))) bf16 halo[HP * CT];
+    __shared__ __attribute__((aligned(16))) bf16 wl[WLDS ? WE * 8 : 8];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int nbx = x.w / BX, nby = x.h / BY, nbz = x.d / BZ;
+    auto swz = [](int hx, int c8) { return c8 ^ ((hx / XSPAN) & (NC - 1)); };
     // work order: output-channel blocks of a brick adjacent, then bricks x-fastest
     const unsigned ncb = gridDim.y;
     const unsigned v = xcd_contiguous(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * ncb);
     int bi = (int)(v / ncb);
-    const int bxi = bi % nbx;
+    const int X0 = bi % nbx * BX;
     bi /= nbx;
-    const int byi = bi % nby;
+    const int Y0 = bi % nby * BY;
     bi /= nby;
-    const int bzi = bi % nbz;
+    const int Z0 = bi % nbz * BZ;
     const int n = bi / nbz;
-    const int X0 = bxi * BX, Y0 = byi * BY, Z0 = bzi * BZ;
     const int co0 = (int)(v % ncb) * 16 * NO;
     const int ci = x.c, K = 27 * ci;
-    const bf16 *xp = reinterpret_cast<const bf16 *>(x.p) + x.coff;
-    const bf16 *wrow = W + (int64_t)(co0 + col) * K;
+    // offsets of the input in 16-byte chunks, 32 bits per batch item (host-checked)
+    const int ct8 = x.ctot >> 3;
+    const bf16x8 *xp = reinterpret_cast<const bf16x8 *>(reinterpret_cast<const bf16 *>(x.p) + x.coff) +
+                       (int64_t)n * x.d * x.h * x.w * ct8;
     const bf16x8 zero = {};
+
+    // this lane's part of a row: interior position xl, chunk rc8, sub-row
+    const int xl = (lane % LR) / NC, rc8 = lane % NC, sub = lane / LR;
+    const int offx = (X0 + xl) * ct8 + rc8;
+    const int rdst = ((wave * RPW + sub) * HX + 1 + xl) * CT + 8 * swz(1 + xl, rc8);
+    auto row_off = [&](int row) {                         // chunk offset of a halo row, -1: zero
+        const int gy = edge(Y0 - 1 + row % HY, x.h, pmask & 2), gz = edge(Z0 - 1 + row / HY, x.d, pmask & 4);
+        return row < ROWS && gy >= 0 && gz >= 0 ? (gz * x.h + gy) * x.w * ct8 : -1;
+    };
+    bf16x8 hv[NL + NS], wv[WLDS ? NW : 1];
+    // every load of this thread is issued before the first LDS store, so a
+    // chunk costs one memory latency, not one per element
+    auto load = [&](int c0) {
+        const int gpt = (ci - c0) >> 3;                   // channel groups left (chunks past it are zero)
+        const bf16x8 *xc = xp + (c0 >> 3);
+        #pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            int ro = row_off((k * 4 + wave) * RPW);
+            #pragma unroll
+            for (int r = 1; r < RPW; ++r) {
+                const int o = row_off((k * 4 + wave) * RPW + r);
+                ro = sub == r ? o : ro;
+            }
+            hv[k] = zero;
+            if (ro >= 0 && rc8 < gpt) hv[k] = xc[(unsigned)(ro + offx)];
+        }
+        #pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            const int e = (int)threadIdx.x + 256 * k, row = e / (2 * NC), j = e % (2 * NC);
+            const int ro = row_off(row), gx = edge(j / NC ? X0 + BX : X0 - 1, x.w, pmask & 1);
+            hv[NL + k] = zero;
+            if (ro >= 0 && gx >= 0 && j % NC < gpt) hv[NL + k] = xc[(unsigned)(ro + gx * ct8 + j % NC)];
+        }
+        if constexpr (WLDS) {
+            #pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                const int e = (int)threadIdx.x + 256 * k, c8 = e % NC, o = e / NC % (16 * NO), t = e / (16 * NO * NC);
+                wv[k] = zero;
+                if (e < WE && c8 < gpt)
+                    wv[k] = *reinterpret_cast<const bf16x8 *>(W + (int64_t)(co0 + o) * K + t * ci + c0 + 8 * c8);
+            }
+        }
+    };
+    auto store = [&]() {
+        #pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if ((k * 4 + wave) * RPW + sub < ROWS)
+                *reinterpret_cast<bf16x8 *>(&halo[rdst + k * 4 * RPW * HX * CT]) = hv[k];
+        #pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            const int e = (int)threadIdx.x + 256 * k, row = e / (2 * NC), j = e % (2 * NC);
+            const int hx = j / NC ? HX - 1 : 0;
+            if (e < SIDE) *reinterpret_cast<bf16x8 *>(&halo[(row * HX + hx) * CT + 8 * swz(hx, j % NC)]) = hv[NL + k];
+        }
+        if constexpr (WLDS)
+            #pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                const int e = (int)threadIdx.x + 256 * k, c8 = e % NC, oc = e / NC;
+                if (e < WE) *reinterpret_cast<bf16x8 *>(&wl[(oc * NC + swz(oc & 15, c8)) * 8]) = wv[k];
+            }
+    };
+
     f32x4 acc[NO][NF];
     #pragma unroll
     for (int o = 0; o < NO; ++o)
         #pragma unroll
         for (int i = 0; i < NF; ++i) acc[o][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bf16 *wrow = W + (int64_t)(co0 + col) * K;
 
+    if (WLDS) load(0);
     for (int c0 = 0; c0 < ci; c0 += CT) {
-        const int gpt = min(CT, ci - c0) >> 3;           // 8-channel groups per tap in this chunk
-        const int lgp = gpt == 1 ? 0 : (gpt == 2 ? 1 : 2);
-        // stage the halo: every load of this thread is issued before the first
-        // LDS store, so the chunk costs one memory latency, not one per element
-        constexpr int PER = (HP * (CT / 8) + 255) / 256;
-        bf16x8 hv[PER];
-        int hdst[PER];
-        #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = (int)threadIdx.x + 256 * k;
-            hdst[k] = -1;
-            hv[k] = zero;
-            if (e < (HP << lgp)) {
-                const int hp = e >> lgp, c8 = e & (gpt - 1);
-                const int hx = hp % HX, hy = (hp / HX) % HY, hz = hp / (HX * HY);
-                int gx = X0 - 1 + hx, gy = Y0 - 1 + hy, gz = Z0 - 1 + hz;
-                bool ok = true;
-                if (gx < 0 || gx >= x.w) {
-                    if (pmask & 1) gx = gx < 0 ? gx + x.w : gx - x.w;
-                    else ok = false;
-                }
-                if (gy < 0 || gy >= x.h) {
-                    if (pmask & 2) gy = gy < 0 ? gy + x.h : gy - x.h;
-                    else ok = false;
-                }
-                if (gz < 0 || gz >= x.d) {
-                    if (pmask & 4) gz = gz < 0 ? gz + x.d : gz - x.d;
-                    else ok = false;
-                }
-                hdst[k] = hp * LROW + 8 * swz(hx, c8);
-                if (ok)
-                    hv[k] = *reinterpret_cast<const bf16x8 *>(
-                        xp + ((((int64_t)n * x.d + gz) * x.h + gy) * x.w + gx) * x.ctot + c0 + 8 * c8);
-            }
-        }
+        if (!WLDS) load(c0);
         __syncthreads();                                  // previous chunk's fragment reads are done
-        #pragma unroll
-        for (int k = 0; k < PER; ++k)
-            if (hdst[k] >= 0) *reinterpret_cast<bf16x8 *>(&halo[hdst[k]]) = hv[k];
+        store();
         __syncthreads();
+        if (WLDS && c0 + CT < ci) load(c0 + CT);
+        const int g = min(CT, ci - c0) >> 3, lg = g == 1 ? 0 : (g == 2 ? 1 : 2), gpt = 1 << lg;
+        // weights of tap t, channel group c8 of this chunk, output block o
+        auto weight = [&](int t, int c8, int o) {
+            if constexpr (WLDS)
+                return *reinterpret_cast<const bf16x8 *>(&wl[((t * 16 * NO + 16 * o + col) * NC + swz(col, c8)) * 8]);
+            else return *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * o * K + t * ci + c0 + 8 * c8);
+        };
         if constexpr (DYR) {
-            // The three dy taps of a (dz, dx, channel group) read the same
-            // halo rows shifted by one: a lane loads the 6 rows its 4 output
-            // rows need once and feeds them to three K blocks (dy = -1, 0, 1),
-            // half the LDS fragment reads of one read per MFMA row and tap.
-            // Super-block s gives lane group grp the combination q = 4 s + grp
-            // of (dz, dx, c8); combinations past the last get zero weights.
-            const int Q9 = 9 * gpt, nsb = (Q9 + 3) >> 2, lg = lgp;
-            auto rows = [&](int s, bf16x8 (&R)[ZW][6]) {
+            // Super-block s gives lane group grp the combination q = 4 s + grp of
+            // (dz, dx, c8); combinations past the last get zero weights.
+            const int Q9 = 9 * gpt, nsb = (Q9 + 3) >> 2;
+            auto rows = [&](int s, int z, bf16x8 (&R)[NR]) {
                 const int q = min(4 * s + grp, Q9 - 1);
                 const int c8 = q & (gpt - 1), dzx = q >> lg;
-                const int dz = dzx / 3, dx = dzx % 3;                 // 0..2: offsets + 1
-                const int hx = col + dx;
+                const int dz = dzx / 3, hx = col + dzx % 3;                 // offsets + 1
+                const bf16 *p = &halo[((wave * ZW + z + dz) * HY * HX + hx) * CT + 8 * swz(hx, c8)];
                 #pragma unroll
-                for (int z = 0; z < ZW; ++z)
-                    #pragma unroll
-                    for (int r = 0; r < 6; ++r) {
-                        const int hp = ((wave * ZW + z + dz) * HY + r) * HX + hx;
-                        R[z][r] = *reinterpret_cast<const bf16x8 *>(&halo[hp * LROW + 8 * swz(hx, c8)]);
-                    }
+                for (int r = 0; r < NR; ++r) R[r] = *reinterpret_cast<const bf16x8 *>(p + r * HX * CT);
             };
             auto wts = [&](int s, bf16x8 (&A)[3][NO]) {
                 const int q4 = 4 * s + grp, q = min(q4, Q9 - 1);
                 const int c8 = q & (gpt - 1), dzx = q >> lg;
-                const int dz = dzx / 3, dx = dzx % 3;
+                const int tap0 = dzx / 3 * 9 + dzx % 3;
                 #pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const int tap = dz * 9 + d * 3 + dx;
+                for (int d = 0; d < 3; ++d)
                     #pragma unroll
                     for (int o = 0; o < NO; ++o) {
-                        const bf16x8 v = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * o * K + tap * ci + c0 + 8 * c8);
-                        A[d][o] = q4 < Q9 ? v : zero;
+                        const bf16x8 a = weight(tap0 + 3 * d, c8, o);
+                        A[d][o] = q4 < Q9 ? a : zero;
                     }
-                }
             };
-            auto mma3 = [&](const bf16x8 (&R)[ZW][6], const bf16x8 (&A)[3][NO]) {
+            auto mma = [&](int z, const bf16x8 (&R)[NR], const bf16x8 (&A)[3][NO]) {
                 #pragma unroll
                 for (int d = 0; d < 3; ++d)
                     #pragma unroll
                     for (int o = 0; o < NO; ++o)
                         #pragma unroll
-                        for (int i = 0; i < NF; ++i) acc[o][i] = mfma(A[d][o], R[i / 4][i % 4 + d], acc[o][i]);
+                        for (int f = 0; f < BY; ++f) acc[o][z * BY + f] = mfma(A[d][o], R[f + d], acc[o][z * BY + f]);
             };
-            bf16x8 R0[ZW][6], R1[ZW][6], A0[3][NO], A1[3][NO];
-            rows(0, R0);
-            wts(0, A0);
+            // register sets in turn, so a plane's MFMAs never wait for the fetch
+            // issued after them; the fetch past the end re-reads a valid block.
+            // 16-channel chunks fetch their weights at use: the registers saved
+            // let one more workgroup stay on the CU, which hides more (16 -> 16
+            // channels on the 128 x 128 x 512 box 266 -> 254 us).
+            constexpr bool AHEAD = CT != 16;
+            bf16x8 R0[NR], R1[NR], A0[3][NO], A1[3][NO];
+            auto step = [&](int s, bf16x8 (&Rc)[NR], bf16x8 (&Rn)[NR], bf16x8 (&Ac)[3][NO], bf16x8 (&An)[3][NO]) {
+                const int sn = min(s + 1, nsb - 1);
+                if constexpr (AHEAD) wts(sn, An);
+                else wts(s, Ac);
+                if constexpr (ZW == 2) {
+                    rows(s, 1, Rn);
+                    mma(0, Rc, Ac);
+                    rows(sn, 0, Rc);
+                    mma(1, Rn, Ac);
+                } else {
+                    rows(sn, 0, Rn);
+                    mma(0, Rc, Ac);
+                }
+            };
+            rows(0, 0, R0);
+            if constexpr (AHEAD) wts(0, A0);
             int s = 0;
             for (; s + 2 <= nsb; s += 2) {
-                rows(s + 1, R1);
-                wts(s + 1, A1);
-                mma3(R0, A0);
-                const int sn = min(s + 2, nsb - 1);
-                rows(sn, R0);
-                wts(sn, A0);
-                mma3(R1, A1);
+                step(s, R0, R1, A0, A1);
+                if constexpr (ZW == 2) step(s + 1, R0, R1, A1, A0);
+                else step(s + 1, R1, R0, A1, A0);
             }
-            if (s < nsb) mma3(R0, A0);
-            continue;
-        }
-        // K blocks of 4 (tap, 8-channel group) pairs.  The full blocks run
-        // unmasked; a last partial block (27 gpt not a multiple of 4) zeroes
-        // the weights of its idle lanes.
-        const int G = 27 * gpt, nfull = G >> 2, rem = G & 3, lg = lgp;
-        auto fetch = [&](int g, bf16x8 (&a)[NO], bf16x8 (&b)[NF]) {
-            const int tap = g >> lg, c8 = g & (gpt - 1);
-            const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-            #pragma unroll
-            for (int o = 0; o < NO; ++o)
-                a[o] = *reinterpret_cast<const bf16x8 *>(wrow + (int64_t)16 * o * K + tap * ci + c0 + 8 * c8);
-            #pragma unroll
-            for (int i = 0; i < NF; ++i) {
-                const int zl = wave * ZW + i / 4, yl = i % 4;
-                const int hx = col + 1 + dx;
-                const int hp = ((zl + 1 + dz) * HY + (yl + 1 + dy)) * HX + hx;
-                b[i] = *reinterpret_cast<const bf16x8 *>(&halo[hp * LROW + 8 * swz(hx, c8)]);
+            if (s < nsb) step(s, R0, R1, A0, A1);
+        } else {
+            // K blocks of 4 (tap, 8-channel group) pairs.  The full blocks run
+            // unmasked; a last partial block (27 gpt not a multiple of 4) zeroes
+            // the weights of its idle lanes.
+            const int G = 27 * gpt, nfull = G >> 2, rem = G & 3;
+            auto fetch = [&](int q, bf16x8 (&a)[NO], bf16x8 (&b)[NF]) {
+                const int tap = q >> lg, c8 = q & (gpt - 1);
+                const int dz = tap / 9, dy = (tap / 3) % 3, hx = col + tap % 3;
+                #pragma unroll
+                for (int o = 0; o < NO; ++o) a[o] = weight(tap, c8, o);
+                #pragma unroll
+                for (int i = 0; i < NF; ++i)
+                    b[i] = *reinterpret_cast<const bf16x8 *>(
+                        &halo[(((wave * ZW + i / BY + dz) * HY + i % BY + dy) * HX + hx) * CT + 8 * swz(hx, c8)]);
+            };
+            auto mma = [&](const bf16x8 (&a)[NO], const bf16x8 (&b)[NF]) {
+                #pragma unroll
+                for (int o = 0; o < NO; ++o)
+                    #pragma unroll
+                    for (int i = 0; i < NF; ++i) acc[o][i] = mfma(a[o], b[i], acc[o][i]);
+            };
+            bf16x8 a[NO], b[NF], a1[NO], b1[NF];
+            fetch(grp, a, b);
+            int kb = 0;
+            for (; kb + 2 <= nfull; kb += 2) {
+                fetch(((kb + 1) << 2) + grp, a1, b1);
+                mma(a, b);
+                fetch((min(kb + 2, nfull - 1) << 2) + grp, a, b);
+                mma(a1, b1);
             }
-        };
-        // two register sets in turn, so a block's MFMAs never wait for the
-        // fetch issued after them; the fetch past the end re-reads a valid block
-        auto mma = [&](const bf16x8 (&a)[NO], const bf16x8 (&b)[NF]) {
-            #pragma unroll
-            for (int o = 0; o < NO; ++o)
+            if (kb < nfull) mma(a, b);
+            if (rem) {
+                const bool valid = grp < rem;
+                fetch(valid ? (nfull << 2) + grp : G - 1, a, b);
                 #pragma unroll
-                for (int i = 0; i < NF; ++i) acc[o][i] = mfma(a[o], b[i], acc[o][i]);
-        };
-        bf16x8 a[NO], b[NF], a1[NO], b1[NF];
-        fetch(grp, a, b);
-        int kb = 0;
-        for (; kb + 2 <= nfull; kb += 2) {
-            fetch(((kb + 1) << 2) + grp, a1, b1);
-            mma(a, b);
-            fetch((min(kb + 2, nfull - 1) << 2) + grp, a, b);
-            mma(a1, b1);
-        }
-        if (kb < nfull) mma(a, b);
-        if (rem) {
-            const bool valid = grp < rem;
-            fetch(valid ? (nfull << 2) + grp : G - 1, a, b);
-            #pragma unroll
-            for (int o = 0; o < NO; ++o) {
-                if (!valid) a[o] = zero;
-                #pragma unroll
-                for (int i = 0; i < NF; ++i) acc[o][i] = mfma(a[o], b[i], acc[o][i]);
+                for (int o = 0; o < NO; ++o)
+                    if (!valid) a[o] = zero;
+                mma(a, b);
             }
         }
     }
-    // A lane holds 4 consecutive output channels of each position: stored as
-    // one 8-byte (BF16) or 16-byte (FP32) access when the slice allows it.
-    const bool vy = y.p && ((y.ctot | y.coff) & 3) == 0;
-    const bool v32 = y32.p && ((y32.ctot | y32.coff) & 3) == 0;
     #pragma unroll
     for (int o = 0; o < NO; ++o) {
         const int oc0 = co0 + 16 * o + (grp << 2);
-        const int nbias = max(y.p ? y.c : 0, y32.p ? y32.c : 0);
-        float bo[4];
-        #pragma unroll
-        for (int j = 0; j < 4; ++j) bo[j] = bias && oc0 + j < nbias ? bias[oc0 + j] : 0.f;
-        const bool fy = vy && oc0 + 3 < y.c, f32 = v32 && oc0 + 3 < y32.c;
+        const f32x4 bo = bias4(bias, oc0, y, y32);
         #pragma unroll
         for (int i = 0; i < NF; ++i) {
-            const int zl = wave * ZW + i / 4, yl = i % 4;
-            const int64_t pb = (((int64_t)n * x.d + Z0 + zl) * x.h + Y0 + yl) * x.w + X0 + col;
-            f32x4 v;
-            #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = relu ? fmaxf(acc[o][i][j] + bo[j], 0.f) : acc[o][i][j] + bo[j];
-            if (fy) {
-                const bf16x4 q = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
-                *reinterpret_cast<bf16x4 *>(reinterpret_cast<bf16 *>(y.p) + pb * y.ctot + y.coff + oc0) = q;
-            } else if (y.p) {
-                #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (oc0 + j < y.c) reinterpret_cast<bf16 *>(y.p)[pb * y.ctot + y.coff + oc0 + j] = (bf16)v[j];
-            }
-            if (f32) {
-                f32x4 *out = reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(y32.p) + pb * y32.ctot + y32.coff + oc0);
-                *out = accumulate ? *out + v : v;
-            } else if (y32.p) {
-                #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (oc0 + j < y32.c) {
-                        float *out = reinterpret_cast<float *>(y32.p) + pb * y32.ctot + y32.coff + oc0 + j;
-                        *out = accumulate ? *out + v[j] : v[j];
-                    }
-            }
+            const int64_t pb = (((int64_t)n * x.d + Z0 + wave * ZW + i / BY) * x.h + Y0 + i % BY) * x.w + X0 + col;
+            store_out(y, y32, pb, oc0, acc[o][i] + bo, relu, accumulate);
         }
     }
 }
 
-template <int NO, int ZW, int CT>
-static void launch_brick(const sg_view *x, const void *w, const float *bias, int co, int pmask, int relu,
-                         const sg_view &y, const sg_view &y32, int accumulate, hipStream_t st)
+// Convolution straight from memory, for extents without whole bricks and for
+// 1x1x1 layers: every wave owns NO x 16 output channels x FP x 16 consecutive
+// positions and walks the K blocks in order (4 consecutive 8-channel groups of the
+// tap-major, channel-minor K axis).  Its operands come from L1 and L2 (16 bytes
+// per lane and fragment), whose latency a ring of D blocks in flight covers; the
+// offsets of a position's taps are computed once per workgroup into an LDS
+// table, and taps outside the box read past the buffer's end, which gives zero.
+// Deep layers of small boxes have few positions, so the host takes few per wave
+// there: 64 -> 128 channels on 4 x 8^3 positions 66 us with one block ahead and
+// 64 positions per wave, 21.5 now; 48 -> 16 on 200 x 104 x 104 633, 383.
+template <int NO, int FP, int D>
+__global__ __launch_bounds__(256) void k_conv_direct(sg_view x, const bf16 *__restrict__ W, int co_all,
+                                                     const float *__restrict__ bias, int k, int pmask, int relu,
+                                                     sg_view y, sg_view y32, int accumulate)
 {
-    const unsigned nb = (unsigned)((int64_t)x->n * (x->d / (4 * ZW)) * (x->h / BY) * (x->w / BX));
-    // row reuse across the dy taps where it measured faster: one output block
-    // (the full-resolution 16-channel layers: 364 -> 321 us on the 128 x 128 x
-    // 512 box) and one-plane 32-channel chunks; the two-plane two-block forms
-    // need 156-164 registers for it and lose occupancy (102 -> 143 us)
-    constexpr bool dyr = NO == 1 || (ZW == 1 && CT == 32);
-    hipLaunchKernelGGL((k_conv3_brick<NO, ZW, CT, dyr>), dim3(nb, co / (16 * NO)), dim3(256), 0, st, *x,
-                       (const bf16 *)w, bias, pmask, relu, y, y32, accumulate);
+    constexpr int NP = 64 * FP;                            // positions of a workgroup
+    __shared__ unsigned tab[27][NP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int P = (int)npos(x), p0 = (int)blockIdx.x * NP;
+    const int co0 = blockIdx.y * 16 * NO;
+    const int ci = x.c, g8 = ci >> 3, taps = k * k * k, K8 = taps * g8, nkb = (K8 + 3) >> 2;
+    constexpr unsigned OUT = 0xfffffff0u;                  // beyond any buffer
+    for (int e = threadIdx.x; e < NP; e += 256) {
+        const bool ok = p0 + e < P;
+        const Pos q = decode(x, ok ? p0 + e : 0);
+        for (int t = 0; t < taps; ++t) {
+            int dz, dy, dx;
+            tap_offset(t, k, dz, dy, dx);
+            const int64_t src = ok ? shifted(x, q, dz, dy, dx, pmask) : -1;
+            tab[t][e] = src < 0 ? OUT : (unsigned)((src * x.ctot + x.coff) * 2);
+        }
+    }
+    __syncthreads();
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        x.p, (short)0, (int)(unsigned)((int64_t)P * x.ctot * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16 *>(W), (short)0, (int)(unsigned)((int64_t)co_all * K8 * 16), 0x00020000);
+    auto ld = [](__amdgpu_buffer_rsrc_t r, unsigned off) {
+        return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+    };
+    f32x4 acc[NO][FP];
+    #pragma unroll
+    for (int o = 0; o < NO; ++o)
+        #pragma unroll
+        for (int i = 0; i < FP; ++i) acc[o][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // this lane's group of the next block to load: g = 4 kb + grp = tap g8 + c8
+    int gl = grp, tap = grp / g8, c8 = grp % g8;
+    const int dt = 4 / g8, dc = 4 % g8;
+    const int pl = wave * 16 * FP + col;
+    const unsigned wrow = (unsigned)(co0 + col) * (unsigned)K8 * 16u;
+    // the ring holds 32-bit words (16-bit elements carried around the loop cost
+    // a copy, and with it a wait, per trip)
+    i32x4 a[D][NO], b[D][FP];
+    auto load = [&](i32x4 (&av)[NO], i32x4 (&bv)[FP]) {
+        const bool in = gl < K8;
+        #pragma unroll
+        for (int o = 0; o < NO; ++o) av[o] = ld(rw, in ? wrow + (unsigned)(16 * o * K8 + gl) * 16u : OUT);
+        const int t = min(tap, taps - 1);
+        #pragma unroll
+        for (int i = 0; i < FP; ++i) {
+            const unsigned off = tab[t][pl + 16 * i];
+            bv[i] = ld(rx, in && off != OUT ? off + 16u * (unsigned)c8 : OUT);
+        }
+        gl += 4;
+        tap += dt;
+        c8 += dc;
+        if (c8 >= g8) {
+            c8 -= g8;
+            ++tap;
+        }
+    };
+    #pragma unroll
+    for (int j = 0; j < D; ++j) load(a[j], b[j]);
+    for (int kb = 0; kb < nkb; kb += D) {
+        #pragma unroll
+        for (int j = 0; j < D; ++j) {
+            // blocks past the last hold zeros
+            #pragma unroll
+            for (int o = 0; o < NO; ++o)
+                #pragma unroll
+                for (int i = 0; i < FP; ++i)
+                    acc[o][i] = mfma(__builtin_bit_cast(bf16x8, a[j][o]), __builtin_bit_cast(bf16x8, b[j][i]), acc[o][i]);
+            load(a[j], b[j]);
+        }
+    }
+    #pragma unroll
+    for (int o = 0; o < NO; ++o) {
+        const int oc0 = co0 + 16 * o + (grp << 2);
+        const f32x4 bo = bias4(bias, oc0, y, y32);
+        #pragma unroll
+        for (int i = 0; i < FP; ++i)
+            if (p0 + pl + 16 * i < P) store_out(y, y32, p0 + pl + 16 * i, oc0, acc[o][i] + bo, relu, accumulate);
+    }
+}
+
+struct ConvArgs {
+    const sg_view *x;
+    const void *w;
+    const float *bias;
+    int co, pmask, relu;
+    sg_view y, y32;
+    int accumulate;
+    hipStream_t st;
+};
+
+template <int NO, int BZ, int CT, bool DYR, bool WLDS>
+static void launch_conv3(const ConvArgs &a)
+{
+    const sg_view *x = a.x;
+    const int nbx = x->w / 16, nby = x->h / 4, nbz = x->d / BZ;
+    hipLaunchKernelGGL((k_conv3<NO, BZ, CT, DYR, WLDS>), dim3((unsigned)((int64_t)x->n * nbx * nby * nbz), a.co / (16 * NO)),
+                       dim3(256), 0, a.st, *x, (const bf16 *)a.w, a.bias, a.pmask, a.relu, a.y, a.y32, a.accumulate,
+                       nbx, nby, nbz);
+}
+
+template <int NO, int FP, int D>
+static void launch_direct(const ConvArgs &a, int k)
+{
+    const int64_t P = (int64_t)a.x->n * a.x->d * a.x->h * a.x->w;
+    hipLaunchKernelGGL((k_conv_direct<NO, FP, D>), dim3((unsigned)((P + 64 * FP - 1) / (64 * FP)), a.co / (16 * NO)),
+                       dim3(256), 0, a.st, *a.x, (const bf16 *)a.w, a.co, a.bias, k, a.pmask, a.relu, a.y, a.y32,
+                       a.accumulate);
 }
 
 // 1x1x1 convolution with few outputs (the network head): one position per
@@ -483,115 +661,184 @@ __global__ void k_weight_prep(const float *w32, int co, int ci, int k, bf16 *wb,
 
 // ------------------------------------------------------ weight gradient
 // dW[co][tap ci + c] = sum_p dy[p][co] x[p + off(tap)][c].  The contraction
-// runs over positions, which are not contiguous in the channels-last tensors,
-// so each workgroup stages a chunk of BPC positions in LDS transposed to
-// position-fastest rows: dy for its 16 NOB output channels and, for every tap,
-// the shifted x rows of its 16-channel input block.  The MFMA then reads
-// A = dy^T (16 co x 32 positions) and B = x (32 positions x 16 channels) as
-// 16-byte rows.  Wave w owns taps w, w + 4, ...; its accumulators stay in
-// registers over all chunks of its position group (grid.x), and each group
-// writes one partial sum per weight to ws[group][co_pad][K].
-constexpr int BPC = 64;              // positions per staged chunk
-constexpr int BROW = BPC + 8;        // LDS row length (bf16), padded against bank conflicts
-constexpr int BTAPS = 7;             // taps per wave (27 taps over 4 waves)
+// runs over positions, so both MFMA operands need 8 positions of one channel
+// per lane while the tensors are channels-last.  A workgroup stages a brick of
+// 256 positions as it lies in memory (16 channels, 32 bytes, per position and
+// channel block): dy, and x with its one-node halo.  Fragments are then read by
+// ds_read_b64_tr_b16, which transposes 4 positions x 16 channels per 16 lanes,
+// so a tap is only another LDS offset: x goes to LDS once instead of once per
+// tap, and nothing is transposed by 2-byte stores.  (Before, staging wrote
+// every tap's rows transposed, 55 KB of LDS stores per 64 positions: 16 -> 16
+// channels on 4 x 64^3 positions 247 us with the reduction, 50 now; 48 -> 16 791,
+// 164; 64 -> 64 on 4 x 16^3 65, 29.)  Within a K block of 32 positions lane group g and
+// read r cover brick positions 16 r + 4 g .. + 3, the same for both operands.
+// Wave w owns taps w, w + 4, ...; its accumulators stay in registers over all
+// bricks of its group (a contiguous run), the next brick's loads are issued
+// before the current brick's MFMAs, and each group writes one partial sum per
+// weight to ws[group][co_pad][K].  Extents need not be multiples of the brick:
+// positions beyond the box carry dy = 0.
+constexpr int WP = 256;              // positions per brick
+constexpr int WTAPS = 7;             // taps per wave (27 taps over 4 waves)
 
-template <int NOB>
-__global__ __launch_bounds__(256) void k_conv_bwd_w(sg_view x, sg_view dy, int k, int pmask, int groups, int co_pad,
-                                                    float *ws, float *wsb)
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// 8 positions of channel (lane & 15): two transposed reads of 4 positions
+__device__ inline bf16x8 read_tr(const bf16 *r0, const bf16 *r1)
 {
-    __shared__ __attribute__((aligned(16))) bf16 xs[27][16][BROW];
-    __shared__ __attribute__((aligned(16))) bf16 dyt[16 * NOB][BROW];
+    typedef __attribute__((address_space(3))) s16x4 *lp;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)r0);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)r1);
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// NOB x NCB blocks of 16 output x 16 input channels per workgroup; BX x BY x
+// BZ = 256 positions per brick (27 taps); K1: a 1x1x1 layer, whose bricks are
+// 256 consecutive positions and whose waves share the K blocks.
+template <int NOB, int NCB, int BX, int BY, int BZ, bool K1>
+__global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, int pmask, int co_pad, int nbx, int nby,
+                                                    int nbz, int64_t nbricks, float *ws, float *wsb)
+{
+    static_assert(BX * BY * BZ == WP && 16 % BX == 0, "brick shape");
+    constexpr int HXW = K1 ? BX : BX + 2, HYW = K1 ? BY : BY + 2, HZW = K1 ? BZ : BZ + 2, HPW = HXW * HYW * HZW;
+    constexpr int XE = 2 * NCB * HPW, XN = (XE + 255) / 256;     // 16-byte chunks of x and their rounds
+    constexpr int DE = 2 * NOB * WP, DN = DE / 256;
+    constexpr int NT = K1 ? 1 : WTAPS;
+    __shared__ __attribute__((aligned(16))) bf16 xs[NCB][HPW][16];
+    __shared__ __attribute__((aligned(16))) bf16 dys[NOB][WP][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, grp = lane >> 4;
-    const int ci = x.c, taps = k * k * k, K = taps * ci;
-    const int co0 = blockIdx.y * 16 * NOB, c0 = blockIdx.z * 16;
-    const int64_t P = npos(x);
-    const int64_t nchunks = (P + BPC - 1) / BPC;
-    const bf16 *xp = reinterpret_cast<const bf16 *>(x.p);
-    const bf16 *dp = reinterpret_cast<const bf16 *>(dy.p);
+    const int ci = x.c, taps = K1 ? 1 : 27, K = taps * ci;
+    const int co0 = blockIdx.y * 16 * NOB, c0 = blockIdx.z * 16 * NCB;
+    const bf16 *xp = reinterpret_cast<const bf16 *>(x.p) + x.coff + c0;
+    const bf16 *dp = reinterpret_cast<const bf16 *>(dy.p) + dy.coff + co0;
     const bf16x8 zero = {};
-    // staging roles: x rows: positions 2m, 2m+1 with m = (tid & 63) / 2, 8-channel
-    // half tid & 1, taps congruent to tid / 64 modulo 4; the two positions of a
-    // channel go to LDS as one 32-bit store
-    const int xpair = (tid & 63) >> 1, xc8 = tid & 1, xtap0 = tid >> 6;
-    const bool xcv = c0 + 8 * xc8 < ci;
-    // dy rows: position tid / (2 NOB), 8-channel group tid % (2 NOB)
-    const int dpos = tid / (2 * NOB), dc8 = tid % (2 * NOB);
-    const int doc = co0 + 8 * dc8;
-    f32x4 acc[BTAPS][NOB], accb[NOB];
-    #pragma unroll
-    for (int t = 0; t < BTAPS; ++t)
+    const int64_t P = npos(x);
+
+    bf16x8 xv[XN], dv[DN];
+    // position of brick b: origin, and (27 taps) its batch item
+    auto load = [&](int64_t b) {
+        int X0 = 0, Y0 = 0, Z0 = 0, n = 0;
+        if constexpr (!K1) {
+            int64_t q = b;
+            X0 = (int)(q % nbx) * BX; q /= nbx;
+            Y0 = (int)(q % nby) * BY; q /= nby;
+            Z0 = (int)(q % nbz) * BZ;
+            n = (int)(q / nbz);
+        }
         #pragma unroll
-        for (int o = 0; o < NOB; ++o) acc[t][o] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < XN; ++k) {
+            const int e = tid + 256 * k;
+            const int hp = e / (2 * NCB), c8 = e % (2 * NCB);
+            bool ok = e < XE && c0 + 8 * c8 < ci;
+            int64_t src;
+            if constexpr (K1) {
+                src = b * WP + hp;
+                ok = ok && src < P;
+            } else {
+                int gx = X0 - 1 + hp % HXW, gy = Y0 - 1 + (hp / HXW) % HYW, gz = Z0 - 1 + hp / (HXW * HYW);
+                // one step beyond the box wraps or is zero, further is not read
+                if (gx < 0 || gx >= x.w) { ok = ok && (pmask & 1) && gx <= x.w; gx = gx < 0 ? x.w - 1 : 0; }
+                if (gy < 0 || gy >= x.h) { ok = ok && (pmask & 2) && gy <= x.h; gy = gy < 0 ? x.h - 1 : 0; }
+                if (gz < 0 || gz >= x.d) { ok = ok && (pmask & 4) && gz <= x.d; gz = gz < 0 ? x.d - 1 : 0; }
+                src = (((int64_t)n * x.d + gz) * x.h + gy) * x.w + gx;
+            }
+            xv[k] = zero;
+            if (ok) xv[k] = *reinterpret_cast<const bf16x8 *>(xp + src * x.ctot + 8 * c8);
+        }
+        #pragma unroll
+        for (int k = 0; k < DN; ++k) {
+            const int e = tid + 256 * k;
+            const int p = e / (2 * NOB), c8 = e % (2 * NOB);
+            bool ok = co0 + 8 * c8 < dy.c;
+            int64_t src;
+            if constexpr (K1) {
+                src = b * WP + p;
+                ok = ok && src < P;
+            } else {
+                const int gx = X0 + p % BX, gy = Y0 + (p / BX) % BY, gz = Z0 + p / (BX * BY);
+                ok = ok && gx < x.w && gy < x.h && gz < x.d;
+                src = (((int64_t)n * x.d + gz) * x.h + gy) * x.w + gx;
+            }
+            dv[k] = zero;
+            if (ok) {
+                dv[k] = *reinterpret_cast<const bf16x8 *>(dp + src * dy.ctot + 8 * c8);
+                #pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (co0 + 8 * c8 + j >= dy.c) dv[k][j] = (bf16)0.f;
+            }
+        }
+    };
+    auto store = [&]() {
+        #pragma unroll
+        for (int k = 0; k < XN; ++k) {
+            const int e = tid + 256 * k, hp = e / (2 * NCB), c8 = e % (2 * NCB);
+            if (e < XE) *reinterpret_cast<bf16x8 *>(&xs[c8 >> 1][hp][8 * (c8 & 1)]) = xv[k];
+        }
+        #pragma unroll
+        for (int k = 0; k < DN; ++k) {
+            const int e = tid + 256 * k, p = e / (2 * NOB), c8 = e % (2 * NOB);
+            *reinterpret_cast<bf16x8 *>(&dys[c8 >> 1][p][8 * (c8 & 1)]) = dv[k];
+        }
+    };
+
+    f32x4 acc[NT][NOB][NCB], accb[NOB];
+    #pragma unroll
+    for (int t = 0; t < NT; ++t)
+        #pragma unroll
+        for (int o = 0; o < NOB; ++o)
+            #pragma unroll
+            for (int c = 0; c < NCB; ++c) acc[t][o][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     #pragma unroll
     for (int o = 0; o < NOB; ++o) accb[o] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the bias gradient is the weight gradient of an input channel of ones;
-    // the wave with the fewest taps computes it in the first input-channel block
-    const bool bias_wave = wsb && blockIdx.z == 0 && wave == taps % 4;
+    // the wave with the fewest taps (K1: every wave, for its K blocks) computes
+    // it in the first input-channel block
+    const bool bias_wave = wsb && blockIdx.z == 0 && (K1 || wave == 3);
     bf16x8 ones;
     #pragma unroll
     for (int j = 0; j < 8; ++j) ones[j] = (bf16)1.f;
+    // a lane's row of a transposed read: position 4 grp + (lane & 15) / 4, channels 4 (lane & 3) ..
+    const int lp = 4 * grp + (col >> 2), lc = 4 * (col & 3);
+    // LDS offset (elements) of this lane's row at K block 0 for read r, and per tap
+    auto hidx = [](int p) { return p % BX + HXW * ((p / BX) % BY + HYW * (p / (BX * BY))); };
+    const int xo0 = hidx(lp) * 16 + lc, xo1 = hidx(lp + 16) * 16 + lc;
+    int to[NT];
+    #pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        const int t = min(wave + 4 * i, 26);
+        to[i] = K1 ? 0 : 16 * (t % 3 + HXW * ((t / 3) % 3 + HYW * (t / 9)));
+    }
 
-    constexpr int XT = 7;                                  // taps per thread: 27 taps over four residues
-    for (int64_t ch = blockIdx.x; ch < nchunks; ch += groups) {
-        const int64_t pbase = ch * BPC;
-        // every load of this thread for the chunk is issued before the barrier
-        // and the LDS stores, so a chunk costs one memory latency
-        bf16x8 xv[XT][2], dv = zero;
-        #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t p = pbase + 2 * xpair + h;
-            const bool pv = p < P;
-            const Pos q = decode(x, pv ? p : 0);
-            #pragma unroll
-            for (int i = 0; i < XT; ++i) {
-                const int t = xtap0 + 4 * i;
-                xv[i][h] = zero;
-                if (t < taps && pv && xcv) {
-                    int dz, dyo, dx;
-                    tap_offset(t, k, dz, dyo, dx);
-                    const int64_t src = shifted(x, q, dz, dyo, dx, pmask);
-                    if (src >= 0)
-                        xv[i][h] = *reinterpret_cast<const bf16x8 *>(xp + src * x.ctot + x.coff + c0 + 8 * xc8);
-                }
-            }
-        }
-        if (dpos < BPC) {
-            const int64_t p = pbase + dpos;
-            if (p < P && doc < dy.c) {
-                dv = *reinterpret_cast<const bf16x8 *>(dp + p * dy.ctot + dy.coff + doc);
-                #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (doc + j >= dy.c) dv[j] = (bf16)0.f;
-            }
-        }
-        __syncthreads();                                   // previous chunk's MFMA reads are done
-        #pragma unroll
-        for (int i = 0; i < XT; ++i) {
-            const int t = xtap0 + 4 * i;
-            if (t < taps)
-                #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const bf16x2 pr = {xv[i][0][j], xv[i][1][j]};
-                    *reinterpret_cast<bf16x2 *>(&xs[t][8 * xc8 + j][2 * xpair]) = pr;
-                }
-        }
-        if (dpos < BPC)
-            #pragma unroll
-            for (int j = 0; j < 8; ++j) dyt[8 * dc8 + j][dpos] = dv[j];
+    const int64_t b0 = nbricks * blockIdx.x / gridDim.x, b1 = nbricks * (blockIdx.x + 1) / gridDim.x;
+    if (b0 < b1) load(b0);
+    for (int64_t b = b0; b < b1; ++b) {
+        __syncthreads();                                   // the previous brick's fragment reads are done
+        store();
         __syncthreads();
+        // planes of this brick inside the box (K blocks beyond it are skipped)
+        const int nz = K1 ? BZ : min(BZ, x.d - (int)(b / ((int64_t)nbx * nby) % nbz) * BZ);
+        if (b + 1 < b1) load(b + 1);
         #pragma unroll
-        for (int ks = 0; ks < BPC / 32; ++ks) {
+        for (int ks = 0; ks < WP / 32; ++ks) {
+            constexpr int KZP = BX * BY / 32;              // K blocks per plane
+            if (K1 ? (ks & 3) != wave : ks / KZP >= nz) continue;
+            const int hk = 16 * (K1 ? 32 * ks : BX == 16 ? HXW * ((2 * ks) % BY + HYW * (ks / KZP))
+                                             : HXW * ((32 / BX * ks) % BY + HYW * (ks / KZP)));
             bf16x8 a[NOB];
             #pragma unroll
-            for (int o = 0; o < NOB; ++o) a[o] = *reinterpret_cast<const bf16x8 *>(&dyt[16 * o + col][32 * ks + 8 * grp]);
+            for (int o = 0; o < NOB; ++o)
+                a[o] = read_tr(&dys[o][32 * ks + lp][lc], &dys[o][32 * ks + 16 + lp][lc]);
             #pragma unroll
-            for (int ti = 0; ti < BTAPS; ++ti) {
-                const int t = wave + 4 * ti;
-                if (t < taps) {
-                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[t][col][32 * ks + 8 * grp]);
+            for (int i = 0; i < NT; ++i) {
+                if (!K1 && i == NT - 1 && wave == 3) continue;     // 27 taps: wave 3 has six
+                #pragma unroll
+                for (int c = 0; c < NCB; ++c) {
+                    const bf16 *xc = &xs[c][0][0] + hk + to[i];
+                    const bf16x8 bb = read_tr(xc + xo0, xc + xo1);
                     #pragma unroll
-                    for (int o = 0; o < NOB; ++o) acc[ti][o] = mfma(a[o], b, acc[ti][o]);
+                    for (int o = 0; o < NOB; ++o) acc[i][o][c] = mfma(a[o], bb, acc[i][o][c]);
                 }
             }
             if (bias_wave)
@@ -599,48 +846,88 @@ __global__ __launch_bounds__(256) void k_conv_bwd_w(sg_view x, sg_view dy, int k
                 for (int o = 0; o < NOB; ++o) accb[o] = mfma(a[o], ones, accb[o]);
         }
     }
+    if constexpr (K1) {
+        // the four waves' sums over their K blocks, added in order through LDS
+        float *red = reinterpret_cast<float *>(&xs[0][0][0]);
+        constexpr int PER = 4 * NOB * (NCB + 1);
+        static_assert(sizeof(float) * 3 * 64 * PER <= sizeof(xs), "the waves' sums must fit the x stage");
+        __syncthreads();
+        if (wave > 0) {
+            float *r = red + ((wave - 1) * 64 + lane) * PER;
+            #pragma unroll
+            for (int o = 0; o < NOB; ++o)
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    #pragma unroll
+                    for (int c = 0; c < NCB; ++c) r[(o * 4 + j) * (NCB + 1) + c] = acc[0][o][c][j];
+                    r[(o * 4 + j) * (NCB + 1) + NCB] = accb[o][j];
+                }
+        }
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 0; w < 3; ++w) {
+            const float *r = red + (w * 64 + lane) * PER;
+            #pragma unroll
+            for (int o = 0; o < NOB; ++o)
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    #pragma unroll
+                    for (int c = 0; c < NCB; ++c) acc[0][o][c][j] += r[(o * 4 + j) * (NCB + 1) + c];
+                    accb[o][j] += r[(o * 4 + j) * (NCB + 1) + NCB];
+                }
+        }
+    }
     if (bias_wave && col == 0)
         #pragma unroll
         for (int o = 0; o < NOB; ++o)
             #pragma unroll
             for (int j = 0; j < 4; ++j) wsb[(int64_t)blockIdx.x * co_pad + co0 + 16 * o + 4 * grp + j] = accb[o][j];
-    // D[4 grp + j][col]: output channel co0 + 16 o + 4 grp + j, input channel c0 + col
-    const int c = c0 + col;
-    if (c >= ci) return;
+    // D[4 grp + j][col]: output channel co0 + 16 o + 4 grp + j, input channel c0 + 16 c + col
     #pragma unroll
-    for (int ti = 0; ti < BTAPS; ++ti) {
-        const int t = wave + 4 * ti;
+    for (int i = 0; i < NT; ++i) {
+        const int t = wave + 4 * i;
         if (t >= taps) continue;
         #pragma unroll
-        for (int o = 0; o < NOB; ++o)
+        for (int c = 0; c < NCB; ++c) {
+            const int ic = c0 + 16 * c + col;
+            if (ic >= ci) continue;
             #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int oc = co0 + 16 * o + 4 * grp + j;
-                ws[((int64_t)blockIdx.x * co_pad + oc) * K + (int64_t)t * ci + c] = acc[ti][o][j];
-            }
+            for (int o = 0; o < NOB; ++o)
+                #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int oc = co0 + 16 * o + 4 * grp + j;
+                    ws[((int64_t)blockIdx.x * co_pad + oc) * K + (int64_t)t * ci + ic] = acc[i][o][c][j];
+                }
+        }
     }
 }
 
-// Fixed-order sum of the per-group partials in two passes: slice s of the
-// groups (g = s, s + S, ...) per thread and output, then the S slice sums.
-__global__ void k_reduce_slices(const float *ws, int groups, int co_pad, int co, int K, int S, float *tmp)
+// Fixed-order sum of the per-group partials of the weights (n values, group
+// stride gs) and the bias (nb values, group stride gsb): 32 outputs x 8 slices of
+// the groups per workgroup, the slices added in order through LDS.
+__global__ __launch_bounds__(256) void k_reduce_groups(const float *__restrict__ ws, int64_t gs, int64_t n,
+                                                       const float *__restrict__ wsb, int gsb, int nb, int groups,
+                                                       float *dw, float *db)
 {
-    const int64_t n = (int64_t)co * K;
-    const int s = blockIdx.y;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int o = (int)(e / K), kc = (int)(e % K);
-        float acc = 0.f;
-        for (int g = s; g < groups; g += S) acc += ws[((int64_t)g * co_pad + o) * K + kc];
-        tmp[(int64_t)s * n + e] = acc;
+    __shared__ float sh[8][32];
+    const int l = threadIdx.x & 31, s = threadIdx.x >> 5;
+    const int64_t e = (int64_t)blockIdx.x * 32 + l;
+    const bool bias = e >= n;
+    const float *src = bias ? wsb + (e - n) : ws + e;
+    const int64_t st = bias ? gsb : gs;
+    float acc = 0.f;
+    if (e < n + nb) {
+        #pragma unroll 4
+        for (int g = s; g < groups; g += 8) acc += src[g * st];
     }
-}
-
-__global__ void k_reduce_final(const float *tmp, int S, int64_t n, float *dw)
-{
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        float acc = 0.f;
-        for (int s = 0; s < S; ++s) acc += tmp[(int64_t)s * n + e];
-        dw[e] = acc;
+    sh[s][l] = acc;
+    __syncthreads();
+    if (s == 0 && e < n + nb) {
+        float v = sh[0][l];
+        #pragma unroll
+        for (int k = 1; k < 8; ++k) v += sh[k][l];
+        if (bias) db[e - n] = v;
+        else dw[e] = v;
     }
 }
 
@@ -957,6 +1244,83 @@ int scratch_on_current_device(float **out)
     return SG_OK;
 }
 
+// Workspace of the weight gradient, as the interface states it (callers size
+// their buffers by it, and sg_conv3d_bwd_weight_noalloc accepts what fits its
+// scratch): partial sums of up to max_groups position groups and some slack.
+struct BwdPlan { int max_groups, co_pad, K; int64_t ws_floats, bias_off; };
+
+static BwdPlan bwd_plan(const sg_view *dy, int ci, int k)
+{
+    BwdPlan b;
+    b.co_pad = (dy->c + 15) & ~15;
+    b.K = k * k * k * ci;
+    const int64_t P = (int64_t)dy->n * dy->d * dy->h * dy->w;
+    const int64_t nchunks = (P + 63) / 64;
+    const int64_t yz = (int64_t)(b.co_pad / (b.co_pad % 32 == 0 ? 32 : 16)) * ((ci + 15) / 16);
+    int64_t g = std::max<int64_t>(1, std::min<int64_t>(nchunks, (1024 + yz - 1) / yz));
+    // keep the partial sums within 64 Mi floats
+    g = std::max<int64_t>(1, std::min<int64_t>(g, ((int64_t)1 << 26) / ((int64_t)b.co_pad * b.K)));
+    b.max_groups = (int)g;
+    b.bias_off = g * b.co_pad * b.K;
+    b.ws_floats = b.bias_off + g * b.co_pad + std::min<int64_t>(16, g) * b.co_pad * ((int64_t)b.K + 1);
+    return b;
+}
+
+template <int NOB, int NCB, int BX, int BY, int BZ, bool K1>
+static void bwd_launch(const sg_view *x, const sg_view *dy, int pmask, float *dw, float *db, float *ws,
+                       const BwdPlan &b, hipStream_t st)
+{
+    const int64_t P = (int64_t)x->n * x->d * x->h * x->w;
+    const int nbx = (x->w + BX - 1) / BX, nby = (x->h + BY - 1) / BY, nbz = (x->d + BZ - 1) / BZ;
+    const int64_t nb = K1 ? (P + WP - 1) / WP : (int64_t)x->n * nbx * nby * nbz;
+    const int gy = b.co_pad / (16 * NOB), gz = (x->c + 16 * NCB - 1) / (16 * NCB);
+    // position groups: as many workgroups as the GPU's 256 CUs hold at once
+    // (registers: 3 per CU with one block pair, else 2), at least one brick each
+    const int target = NOB * NCB == 1 ? 768 : 512;
+    int64_t g = std::min<int64_t>(nb, std::max<int64_t>(1, target / ((int64_t)gy * gz)));
+    g = std::min<int64_t>(g, b.max_groups);
+    float *wsb = db ? ws + b.bias_off : nullptr;
+    hipLaunchKernelGGL((k_conv_bwd_w<NOB, NCB, BX, BY, BZ, K1>), dim3((unsigned)g, gy, gz), dim3(256), 0, st, *x, *dy,
+                       pmask, b.co_pad, nbx, nby, nbz, nb, ws, wsb);
+    const int64_t n = (int64_t)dy->c * b.K;
+    const int nbias = db ? dy->c : 0;
+    hipLaunchKernelGGL(k_reduce_groups, dim3((unsigned)((n + nbias + 31) / 32)), dim3(256), 0, st, (const float *)ws,
+                       (int64_t)b.co_pad * b.K, n, (const float *)wsb, b.co_pad, nbias, (int)g, dw, db);
+}
+
+template <int NOB, int NCB>
+static void bwd_shape(const sg_view *x, const sg_view *dy, int pmask, float *dw, float *db, float *ws,
+                      const BwdPlan &b, hipStream_t st)
+{
+    // the brick that pads the box least (16-wide rows on a tie)
+    auto pad = [&](int bx, int by, int bz) {
+        return (int64_t)((x->w + bx - 1) / bx * bx) * ((x->h + by - 1) / by * by) * ((x->d + bz - 1) / bz * bz);
+    };
+    const int64_t p16 = pad(16, 4, 4), p8 = pad(8, 8, 4), p4 = pad(4, 8, 8);
+    if (p16 <= p8 && p16 <= p4) bwd_launch<NOB, NCB, 16, 4, 4, false>(x, dy, pmask, dw, db, ws, b, st);
+    else if (p8 <= p4) bwd_launch<NOB, NCB, 8, 8, 4, false>(x, dy, pmask, dw, db, ws, b, st);
+    else bwd_launch<NOB, NCB, 4, 8, 8, false>(x, dy, pmask, dw, db, ws, b, st);
+}
+
+// The weight-gradient kernels with the per-group partial sums in ws (at least
+// b.ws_floats floats); shared by the workspace and the no-allocation entries.
+static int bwd_weight_launch(const sg_view *x, const sg_view *dy, int32_t k, int32_t periodic_mask, float *dw,
+                             float *db, float *ws, const BwdPlan &b, hipStream_t st)
+{
+    const int nci = (x->c + 15) / 16;
+    const int64_t P = (int64_t)x->n * x->d * x->h * x->w;
+    if (k == 1) {
+        bwd_launch<1, 1, 16, 4, 4, true>(x, dy, periodic_mask, dw, db, ws, b, st);
+    } else if (b.co_pad % 32 == 0 && nci % 2 == 0 && P / WP * (b.co_pad / 32) * (nci / 2) >= 256) {
+        bwd_shape<2, 2>(x, dy, periodic_mask, dw, db, ws, b, st);
+    } else if (b.co_pad % 32 == 0 && P / WP * (b.co_pad / 32) * nci >= 256) {
+        bwd_shape<2, 1>(x, dy, periodic_mask, dw, db, ws, b, st);
+    } else {
+        bwd_shape<1, 1>(x, dy, periodic_mask, dw, db, ws, b, st);
+    }
+    return status();
+}
+
 }  // namespace sg
 
 using namespace sg;
@@ -972,27 +1336,36 @@ int sg_conv3d_fwd(const sg_view *x, const void *w, const float *bias, int32_t co
     if (y32 && (!ok_view(y32) || !same_pos(x, y32) || y32->c > co)) return SG_EINVAL;
     const sg_view none = {};
     const int64_t P = (int64_t)x->n * x->d * x->h * x->w;
-    if (k == 3 && x->w % BX == 0 && x->h % BY == 0 && x->d % 4 == 0) {
-        hipStream_t st = (hipStream_t)hip_stream;
-        const sg_view yv = y ? *y : none, y32v = y32 ? *y32 : none;
-        const bool deep = x->c % 32 != 0 && x->d % 8 == 0;   // few or odd channel counts: two planes per wave
-        // a 32-channel chunk stages 1, 2 or 4 eight-channel groups per position;
-        // an input channel count of 24 mod 32 would leave a last chunk of 3
-        // groups, so those layers stage 16-channel chunks
-        const bool ct16 = x->c % 32 == 24;
-        // two planes per wave also for 32-channel chunks when that still leaves
-        // at least 512 workgroups (large layers: less halo per output; measured
-        // on the U-Net, smaller layers lose from the fewer workgroups)
-        const bool big = x->d % 8 == 0 && P / (BX * BY * 8) * (co / 32) >= 512;
-        if (co % 32 == 0) {
-            if (deep) launch_brick<2, 2, 16>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
-            else if (ct16) launch_brick<2, 1, 16>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
-            else if (big) launch_brick<2, 2, 32>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
-            else launch_brick<2, 1, 32>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
+    const ConvArgs a{x, w, bias, co, periodic_mask, relu, y ? *y : none, y32 ? *y32 : none, accumulate,
+                     (hipStream_t)hip_stream};
+    const bool bricks = x->w % 16 == 0 && x->h % 4 == 0 && x->d % 4 == 0;
+    if (k == 3 && bricks && (int64_t)x->d * x->h * x->w * (x->ctot / 8) < (int64_t)1 << 31) {
+        // Summation order (chunk length, DYR) by channels and extents alone; the
+        // launch shape within it by size.  Chunks: 16 channels where ci is no
+        // multiple of 32 and two planes per wave fit, or where ci leaves 24 (an
+        // 8-channel layer's one chunk is 8 long); else 32.
+        const bool two = x->d % 8 == 0, few = x->c % 32 != 0 && two, odd = x->c % 32 == 24;
+        // large: two planes per wave for 32-channel chunks when that still leaves
+        // at least 512 workgroups (less halo per output)
+        const bool big = two && P / 512 * (co / 32) >= 512;
+        // Below two workgroups of one output block per CU the weights go through
+        // LDS: 192 -> 64 channels on 4 x 16^3 60 -> 26 us, 64 -> 64 there 22.7 ->
+        // 12.7; above it the larger LDS use costs more (32 -> 64 on 128 x 32 x 32 25
+        // us without, 43 with).
+        const bool small = P / 256 * (co / 16) <= 512;
+        if (co % 32 == 0 && (few || odd)) {
+            if (few) launch_conv3<2, 8, 16, false, false>(a);
+            else launch_conv3<2, 4, 16, false, false>(a);
+        } else if (co % 32 == 0 && big) {
+            launch_conv3<2, 8, 32, false, false>(a);
+        } else if (few || odd) {
+            if (x->c == 8) launch_conv3<1, 8, 8, true, false>(a);
+            else if (few) launch_conv3<1, 8, 16, true, false>(a);
+            else launch_conv3<1, 4, 16, true, false>(a);
         } else {
-            if (deep) launch_brick<1, 2, 16>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
-            else if (ct16) launch_brick<1, 1, 16>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
-            else launch_brick<1, 1, 32>(x, w, bias, co, periodic_mask, relu, yv, y32v, accumulate, st);
+            if (small) launch_conv3<1, 4, 32, true, true>(a);
+            else if (co % 32 == 0) launch_conv3<2, 4, 32, true, false>(a);
+            else launch_conv3<1, 4, 32, true, false>(a);
         }
         return status();
     }
@@ -1000,6 +1373,18 @@ int sg_conv3d_fwd(const sg_view *x, const void *w, const float *bias, int32_t co
     if (k == 1 && nout <= 4 && x->c <= 64) {
         hipLaunchKernelGGL(k_conv1_small<4>, dim3(grid_for(P)), dim3(256), 0, (hipStream_t)hip_stream, *x,
                            (const bf16 *)w, bias, relu, y ? *y : none, y32 ? *y32 : none, accumulate);
+        return status();
+    }
+    // 32-bit byte offsets: tensors and weights below 2^31 bytes
+    if (P * x->ctot * 2 < (int64_t)1 << 31 && (int64_t)co * k * k * k * x->c * 2 < (int64_t)1 << 31) {
+        const int64_t waves = P / 64 * (co / 16);         // at 64 positions and one output block each
+        // two waves per SIMD at 64 positions each keep the reuse of four fragments
+        // per weight fragment; below that 16 positions per wave fill the GPU
+        // (16 -> 16 on 72 x 40 x 40, 1800 waves: 17.6 us, 27 with 16; 64 -> 128 on 4
+        // x 8^3, 256 waves: 21.5, 40 with 64)
+        if (waves >= 2048 && co % 32 == 0) launch_direct<2, 4, 2>(a, k);
+        else if (waves >= 512) launch_direct<1, 4, 3>(a, k);
+        else launch_direct<1, 1, 8>(a, k);
         return status();
     }
     const unsigned gx = (unsigned)((P + 64 * FP - 1) / (64 * FP));
@@ -1025,30 +1410,6 @@ int sg_weight_prep(const float *w32, int32_t co, int32_t ci, int32_t k, void *w_
     return status();
 }
 
-struct BwdPlan { int nob, groups, co_pad, cblocks, K, S; int64_t ws_floats, bias_off, tmp_off, tmpb_off; };
-
-static BwdPlan bwd_plan(const sg_view *dy, int ci, int k)
-{
-    BwdPlan b;
-    b.co_pad = (dy->c + 15) & ~15;
-    b.nob = b.co_pad % 32 == 0 ? 2 : 1;
-    b.cblocks = (ci + 15) / 16;
-    b.K = k * k * k * ci;
-    const int64_t P = (int64_t)dy->n * dy->d * dy->h * dy->w;
-    const int64_t nchunks = (P + BPC - 1) / BPC;
-    const int64_t yz = (int64_t)(b.co_pad / (16 * b.nob)) * b.cblocks;
-    int64_t g = std::max<int64_t>(1, std::min<int64_t>(nchunks, (1024 + yz - 1) / yz));
-    // keep the partial sums within 64 Mi floats
-    g = std::max<int64_t>(1, std::min<int64_t>(g, ((int64_t)1 << 26) / ((int64_t)b.co_pad * b.K)));
-    b.groups = (int)g;
-    b.S = (int)std::min<int64_t>(16, g);
-    b.bias_off = g * b.co_pad * b.K;
-    b.tmp_off = b.bias_off + g * b.co_pad;
-    b.tmpb_off = b.tmp_off + (int64_t)b.S * b.co_pad * b.K;
-    b.ws_floats = b.tmpb_off + (int64_t)b.S * b.co_pad;
-    return b;
-}
-
 int64_t sg_conv3d_bwd_weight_ws(const sg_view *dy, int32_t ci, int32_t k)
 {
     if (!ok_view(dy) || ci <= 0 || (k != 1 && k != 3)) return -1;
@@ -1059,34 +1420,6 @@ static bool bwd_weight_args(const sg_view *x, const sg_view *dy, int32_t k, cons
 {
     return mfma_view(x) && ok_view(dy) && dy->ctot % 8 == 0 && dy->coff % 8 == 0 && dy->c <= 256 && same_pos(x, dy) &&
            dw && (k == 1 || k == 3);
-}
-
-// The weight-gradient kernels with the per-group partial sums in ws (at least
-// b.ws_floats floats); shared by the workspace and the no-allocation entries.
-static int bwd_weight_launch(const sg_view *x, const sg_view *dy, int32_t k, int32_t periodic_mask, float *dw,
-                             float *db, float *ws, const BwdPlan &b, hipStream_t st)
-{
-    const int ci = x->c, co = dy->c;
-    const dim3 grid(b.groups, b.co_pad / (16 * b.nob), b.cblocks);
-    float *wsb = db ? ws + b.bias_off : nullptr;
-    if (b.nob == 2)
-        hipLaunchKernelGGL(k_conv_bwd_w<2>, grid, dim3(256), 0, st, *x, *dy, k, periodic_mask, b.groups, b.co_pad, ws,
-                           wsb);
-    else
-        hipLaunchKernelGGL(k_conv_bwd_w<1>, grid, dim3(256), 0, st, *x, *dy, k, periodic_mask, b.groups, b.co_pad, ws,
-                           wsb);
-    const int64_t nw = (int64_t)co * b.K;
-    hipLaunchKernelGGL(k_reduce_slices, dim3(grid_for(nw), b.S), dim3(256), 0, st, (const float *)ws, b.groups, b.co_pad,
-                       co, b.K, b.S, ws + b.tmp_off);
-    hipLaunchKernelGGL(k_reduce_final, dim3(grid_for(nw)), dim3(256), 0, st, (const float *)(ws + b.tmp_off), b.S, nw, dw);
-    if (db) {
-        hipLaunchKernelGGL(k_reduce_slices, dim3(grid_for(co), b.S), dim3(256), 0, st, (const float *)wsb, b.groups,
-                           b.co_pad, co, 1, b.S, ws + b.tmpb_off);
-        hipLaunchKernelGGL(k_reduce_final, dim3(grid_for(co)), dim3(256), 0, st, (const float *)(ws + b.tmpb_off), b.S,
-                           (int64_t)co, db);
-    }
-    (void)ci;
-    return status();
 }
 
 int sg_conv3d_bwd_weight(const sg_view *x, const sg_view *dy, int32_t k, int32_t periodic_mask, float *dw, float *db,
