@@ -108,22 +108,31 @@ class Conv:
         std = 0.0 if zero else math.sqrt(2.0 / self.K)
         w = rng.standard_normal((co, self.K)).astype(np.float32) * std
         dev = "cuda"
-        self.w = torch.tensor(w, device=dev)
-        self.b = torch.zeros(co, device=dev)
-        self.gw = torch.zeros_like(self.w)
-        self.gb = torch.zeros_like(self.b)
-        self.mw, self.vw = torch.zeros_like(self.w), torch.zeros_like(self.w)
-        self.mb, self.vb = torch.zeros_like(self.b), torch.zeros_like(self.b)
-        self.bias_pad = torch.zeros(self.co_pad, device=dev)
+        # one array each for the parameters, their gradients and Adam's moments:
+        # the weights, then the bias padded to co_pad (the form the kernels read)
+        self.place(*torch.zeros((4, self.numel()), device=dev))
+        self.w.copy_(torch.from_numpy(w))
         self.wb = torch.zeros(self.co_pad * self.K, dtype=torch.bfloat16, device=dev)
         self.wt = torch.zeros(self.ci_pad * k ** 3 * self.co8, dtype=torch.bfloat16, device=dev)
         self.prep()
+
+    def numel(self):
+        return self.co * self.K + self.co_pad
+
+    def place(self, par, grad, m, v):
+        """Take the layer's arrays as views of four flat ones (numel() each)."""
+        n = self.co * self.K
+        split = lambda t: (t[:n].view(self.co, self.K), t[n:n + self.co])
+        (self.w, self.b), (self.gw, self.gb) = split(par), split(grad)
+        (self.mw, self.mb), (self.vw, self.vb) = split(m), split(v)
+        self.bias_pad, self.placed = par[n:], (self.w, self.b, self.gw, self.gb, self.mw, self.vw, self.mb, self.vb)
 
     def prep(self):
         _chk(lib().sg_weight_prep(C.c_void_p(self.w.data_ptr()), self.co, self.ci, self.k,
                                   C.c_void_p(self.wb.data_ptr()), C.c_void_p(self.wt.data_ptr()),
                                   self.co_pad, self.ci_pad, _stream()), "sg_weight_prep")
-        self.bias_pad[: self.co].copy_(self.b)
+        if self.b is not self.placed[1]:              # a bias the caller put in the layer's place
+            self.bias_pad[: self.co].copy_(self.b)
 
     def params(self):
         return [(self.w, self.gw, self.mw, self.vw), (self.b, self.gb, self.mb, self.vb)]
@@ -162,6 +171,15 @@ class UNet:
         self.L["head"] = Conv("head", c1, NF, 1, False, rng, zero=True)
         self.layers = list(self.L.values())
         self.nparams = sum(l.w.numel() + l.b.numel() for l in self.layers)
+        # all layers' parameters, gradients and moments in four flat arrays, so
+        # that an Adam step is one launch (30 before, 3 us each and as many calls)
+        self.flat = torch.zeros((4, sum(l.numel() for l in self.layers)), device="cuda")
+        at = 0
+        for l in self.layers:
+            old, end = l.w, at + l.numel()
+            l.place(*self.flat[:, at:end])
+            l.w.copy_(old)
+            at = end
         s = [(n, d >> i, h >> i, w >> i) for i in range(4)]
         bf = torch.bfloat16
         A = lambda lvl, c, dt=bf: torch.zeros(s[lvl] + (c,), dtype=dt, device="cuda")
@@ -268,11 +286,16 @@ class UNet:
 
     def adam(self, lr, b1=0.9, b2=0.999, eps=1e-8):
         self.step_count += 1
+        if all(a is b for l in self.layers
+               for a, b in zip((l.w, l.b, l.gw, l.gb, l.mw, l.vw, l.mb, l.vb), l.placed)):
+            groups = [tuple(self.flat)]
+        else:                                         # the caller gave a layer tensors of its own
+            groups = [p for l in self.layers for p in l.params()]
+        for w, g, m, v in groups:
+            _chk(lib().sg_adam(C.c_void_p(w.data_ptr()), C.c_void_p(g.data_ptr()), C.c_void_p(m.data_ptr()),
+                               C.c_void_p(v.data_ptr()), w.numel(), lr, b1, b2, eps, self.step_count,
+                               _stream()), "adam")
         for l in self.layers:
-            for w, g, m, v in l.params():
-                _chk(lib().sg_adam(C.c_void_p(w.data_ptr()), C.c_void_p(g.data_ptr()), C.c_void_p(m.data_ptr()),
-                                   C.c_void_p(v.data_ptr()), w.numel(), lr, b1, b2, eps, self.step_count,
-                                   _stream()), "adam")
             l.prep()
 
     # ------------------------------------------------------------- fields
