@@ -80,11 +80,12 @@ template <> struct Storage<LBCG_BF16S> {
     __device__ static T enc(float d, float) { return (T)d; }
 };
 
-// Cache policy of the population streams: loads are non-temporal, so that a
-// pass's stream does not displace the reused per-node arrays (aux stencil,
-// stored densities) from L2; stores are ordinary, so that the level just
-// written is still in the caches when the next pass reads it (measured: FP16S
-// step 152 -> 142 us, FP32 228 -> 221 us on the 128^3 benchmark).
+// Cache policy of the population streams in the two-pass step: loads are
+// non-temporal, so that a pass's stream does not displace the reused per-node
+// arrays (aux stencil, stored densities) from L2; stores are ordinary, so that
+// the level just written is still in the caches when the next pass reads it
+// (measured: FP16S step 152 -> 142 us, FP32 228 -> 221 us on the 128^3
+// benchmark).  The fused step loads ordinarily and stores by size (lbcg_init).
 
 // Buffer-resource access.  A resource (base, size in bytes) is uniform over
 // the wavefront and lives in scalar registers; each lane supplies only a

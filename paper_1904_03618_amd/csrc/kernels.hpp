@@ -1048,20 +1048,58 @@ __device__ inline void fpull_finish(const StepArgs &a, DC &C, const Coord &c, co
     else pull_finish<ST, MV, ROW>(a, C, c, wr.r, ri, p.v, s);
 }
 
+// Pull addresses of a plane without bounce-back (no wall layer), for levels in
+// one buffer resource: the planes zp - 1, zp, zp + 1 and the directions' arrays
+// are scalar offsets, so a lane supplies only its place in the plane, one of
+// nine values (o) that do not change while a tile marches.
+struct PlaneOfs { uint32_t z[3]; };            // first node of planes zp - 1, zp, zp + 1
+
+__device__ inline PlaneOfs plane_ofs(DC &C, int zp)
+{
+    const uint32_t nxy = (uint32_t)(C.nx * C.ny);
+    return {{nxy * (uint32_t)(zp == 0 ? C.nz - 1 : zp - 1), nxy * (uint32_t)zp,
+             nxy * (uint32_t)(zp == C.nz - 1 ? 0 : zp + 1)}};
+}
+
+// In-plane node indices of (gx + X, gy + Y), X, Y in {-1, 0, 1}, periodic wrap.
+__device__ inline void plane_nodes(DC &C, int gx, int gy, uint32_t (&o)[3][3])
+{
+    const int xs[3] = {gx == 0 ? C.nx - 1 : gx - 1, gx, gx == C.nx - 1 ? 0 : gx + 1};
+    const int ys[3] = {C.nx * (gy == 0 ? C.ny - 1 : gy - 1), C.nx * gy, C.nx * (gy == C.ny - 1 ? 0 : gy + 1)};
+    #pragma unroll
+    for (int i = 0; i < 3; ++i)
+        #pragma unroll
+        for (int j = 0; j < 3; ++j) o[i][j] = (uint32_t)(xs[i] + ys[j]);
+}
+
+template <int ST, int IN, int I = 0>
+__device__ inline void plane_issue(__amdgpu_buffer_rsrc_t r, uint32_t NS, const PlaneOfs &zo,
+                                   const uint32_t (&o)[3][3], FPull<ST, IN> &p)
+{
+    if constexpr (I < Q) {
+        using T = typename Storage<ST>::T;
+        using P = typename Storage<ST>::P;
+        const uint32_t n = o[1 - ex(I)][1 - ey(I)], z = zo.z[1 - ez(I)];
+        if constexpr (IN == LV_PAIR) {
+            p.v[I] = buf_ld_so<P, CP_DEFAULT>(r, n * (uint32_t)sizeof(P), (I * NS + z) * (uint32_t)sizeof(P));
+        } else if constexpr (I == 0) {
+            p.v0 = buf_ld_so<P, CP_DEFAULT>(r, n * (uint32_t)sizeof(P), z * (uint32_t)sizeof(P));
+        } else {
+            p.v[I] = buf_ld_so<T, CP_DEFAULT>(r, n * (uint32_t)sizeof(T), ((I + 1) * NS + z) * (uint32_t)sizeof(T));
+        }
+        plane_issue<ST, IN, I + 1>(r, NS, zo, o, p);
+    }
+}
+
 // Position (relative to the tile origin) of entry e of the halo of width h
 // around an ax x ay tile: the 2h rows below and above (w = ax + 2h wide,
 // nrow entries), then the 2h columns beside the tile.
 __device__ inline void halo_pos(int e, int w, int nrow, int h, int ax, int ay, int &rx, int &ry)
 {
-    if (e < nrow) {
-        const int r = e / w;
-        rx = e - r * w - h;
-        ry = r < h ? r - h : ay + (r - h);
-    } else {
-        const int e1 = e - nrow, cc = e1 / ay;
-        ry = e1 - cc * ay;
-        rx = cc < h ? cc - h : ax + (cc - h);
-    }
+    const int r = e / w, xr = e - r * w - h, yr = r < h ? r - h : ay + (r - h);
+    const int e1 = max(e - nrow, 0), cc = e1 / ay, yc = e1 - cc * ay, xc = cc < h ? cc - h : ax + (cc - h);
+    rx = e < nrow ? xr : xc;
+    ry = e < nrow ? yr : yc;
 }
 
 // Position (relative to the tile origin) of entry e of the ring at distance
@@ -1105,24 +1143,39 @@ __device__ inline void fused_ring2(const StepArgs &a, DC &C, float4 *slot, float
     }
 }
 
+// A lane's halo duties around a tile: entries lane and 64 + lane of the
+// one-node halo (84 nodes around a 32 x 8 tile) in the two waves on duty,
+// which rotate by plane.  Positions are found once per tile.
+struct HaloRole { int gx, gy, i; };            // global node column, index in the LDS planes
+static_assert(RH == FH && RW == FRX, "density and aux planes share one index");
+
+__device__ inline HaloRole halo_role(DC &C, int e, int x0, int y0, int ax, int ay)
+{
+    const int w = ax + 2, nrow = 2 * w, nh = nrow + 2 * ay;
+    int rx, ry;
+    halo_pos(min(e, nh - 1), w, nrow, 1, ax, ay, rx, ry);
+    return {(x0 + rx + 4 * C.nx) % C.nx, (y0 + ry + 4 * C.ny) % C.ny, fidx(rx, ry)};
+}
+
 // Aux values of plane zp (0 <= zp < nz) into the ring slot of plane zl (zl =
 // zp, or zp -+ nz for the periodic neighbours of the chunk's end planes): the
-// lane's own node (pulled state kept in s) and the halo of width h (1, or 2
-// on a wall layer).  The one-node halo (84 nodes around a 32 x 8 tile) is
-// smaller than the workgroup, so a lane pulls at most one halo node; the
-// halo duty falls on consecutive waves, rotated by plane.  Lanes outside a
-// ragged tile (and past the halo) pull a valid node and drop the result.  On
-// a wall layer of a case with moving walls the density factor qs of Qbar goes
+// lane's own node (pulled state kept in s) and the one-node halo, at most one
+// node per lane, on the waves on duty.  Lanes outside a ragged tile (and past
+// the halo) drop out.  BB: zp is a wall layer, whose pulls bounce back; on the
+// other planes nothing does, and their code carries none of the selects (the
+// wall and the address selects were 140 of 440 instructions of a pull).  On a
+// wall layer of a case with moving walls the density factor qs of Qbar goes
 // to wq[side] for the ghost layer.
-template <int ST, bool MV, int WL, int IN, bool SO = false>
+template <int ST, bool MV, int WL, int IN, bool SO, bool BB>
 __device__ inline void fused_plane(const StepArgs &a, DC &C, float4 (*ring)[FREG], float2 (*rring)[RREG],
                                    const float4 *dring, const float *cring, float (*wq)[FREG], int zl, int zp,
-                                   int x0, int y0, int ax, int ay, int h, bool active, int tx, int ty,
-                                   NodeState &s)
+                                   int gx, int gy, bool active, int oi, const HaloRole h0, const HaloRole h1,
+                                   int nh, NodeState &s)
 {
-    using P = typename Storage<ST>::P;
+    using S = Storage<ST>;
+    using P = typename S::P;
     float4 *slot = ring[fslot(zl)];
-    const bool wlo = MV && C.wall == 2 && zp == 0, whi = MV && C.wall == 2 && zp == C.nz - 1;
+    const bool wlo = MV && BB && zp == 0, whi = MV && BB && zp == C.nz - 1;
     WriterRing wr;
     #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -1131,82 +1184,73 @@ __device__ inline void fused_plane(const StepArgs &a, DC &C, float4 (*ring)[FREG
         wr.d[k] = dring + (IN == LV_COMPACT ? sl * RREG : 0);
         wr.c[k] = cring + (IN == LV_COMPACT ? sl * RREG : 0);
     }
-    // the one-node ring here; a wall layer's second ring after it (fused_ring2)
-    const int w = ax + 2, nrow = 2 * w, nh = nrow + 2 * ay;
-    const int rot = zl & (FNW - 1);
-    const int e = ((int)threadIdx.x - 64 * rot + FNT) & (FNT - 1);
-    const int wave = (int)threadIdx.x >> 6;
-    const bool wave_halo = __builtin_amdgcn_readfirstlane((((wave - rot) & (FNW - 1)) * 64 < nh) ? 1 : 0) != 0;
-    if constexpr (sizeof(P) == 8 && IN == LV_PAIR) {
-        // FP32 pairs: a wave with halo duty issues both nodes' loads before it
-        // waits (one memory latency instead of two, at 2 waves per SIMD)
-        const int ox = min(tx, ax - 1), oy = min(ty, ay - 1);
-        const Coord co = make_coord_xyz<WL>(C, x0 + ox, y0 + oy, zp);
-        FPull<ST, IN> vo;
-        fpull_issue<ST, IN, CP_DEFAULT, SO>(a, C, co, vo);
-        float qs;
-        if (wave_halo) {
-            const int eh = min(e, nh - 1);
-            int rx, ry;
-            halo_pos(eh, w, nrow, 1, ax, ay, rx, ry);
-            const int gx = (x0 + rx + 4 * C.nx) % C.nx, gy = (y0 + ry + 4 * C.ny) % C.ny;
-            const Coord ch = make_coord_xyz<WL>(C, gx, gy, zp);
-            FPull<ST, IN> vh;
-            fpull_issue<ST, IN, CP_DEFAULT, SO>(a, C, ch, vh);
-            __builtin_amdgcn_sched_barrier(0);   // both nodes' loads issued before the first use
-            fpull_finish<ST, IN, MV>(a, C, co, wr, ridx(ox, oy), vo, s);
-            if (active) {
-                slot[fidx(tx, ty)] = aux_value(C, s, qs);
-                if (wlo) wq[0][fidx(tx, ty)] = qs;
-                if (whi) wq[1][fidx(tx, ty)] = qs;
-            }
-            NodeState hs;
-            fpull_finish<ST, IN, MV>(a, C, ch, wr, ridx(rx, ry), vh, hs);
-            if (e < nh) {
-                slot[fidx(rx, ry)] = aux_value(C, hs, qs);
-                if (wlo) wq[0][fidx(rx, ry)] = qs;
-                if (whi) wq[1][fidx(rx, ry)] = qs;
-            }
+    const int lane = (int)threadIdx.x & 63;
+    const int duty = __builtin_amdgcn_readfirstlane((((int)threadIdx.x >> 6) - zl) & (FNW - 1));
+    const int m = duty == 0 ? -1 : 0;              // (no select between the structs: that would put them in memory)
+    const int hx = (h0.gx & m) | (h1.gx & ~m), hy = (h0.gy & m) | (h1.gy & ~m), hi = (h0.i & m) | (h1.i & ~m);
+    auto issue = [&](int x, int y, FPull<ST, IN> &v) {
+        if constexpr (SO && !BB) {
+            uint32_t o[3][3];
+            plane_nodes(C, x, y, o);
+            const size_t NS = (size_t)C.NS, elems = IN == LV_PAIR ? 38 * NS : 20 * NS;
+            const typename S::T *base = reinterpret_cast<const typename S::T *>(a.fin) + C.pop_off;
+            plane_issue<ST, IN>(rsrc(base, elems * sizeof(typename S::T)), (uint32_t)NS, plane_ofs(C, zp), o, v);
+            Coord c{};
+            return c;
         } else {
-            __builtin_amdgcn_sched_barrier(0);
-            fpull_finish<ST, IN, MV>(a, C, co, wr, ridx(ox, oy), vo, s);
-            if (active) {
-                slot[fidx(tx, ty)] = aux_value(C, s, qs);
-                if (wlo) wq[0][fidx(tx, ty)] = qs;
-                if (whi) wq[1][fidx(tx, ty)] = qs;
-            }
+            const Coord c = make_coord_xyz<BB ? WL : WALLS_NONE>(C, x, y, zp);
+            fpull_issue<ST, IN, CP_DEFAULT, SO>(a, C, c, v);
+            return c;
+        }
+    };
+    auto put = [&](const NodeState &st, int i) {
+        float qs;
+        slot[i] = aux_value(C, st, qs);
+        if (wlo) wq[0][i] = qs;
+        if (whi) wq[1][i] = qs;
+    };
+    const bool duty_lane = duty * 64 + lane < nh;
+    if constexpr (ST == LBCG_FP32) {
+        // FP32 (2 waves per SIMD): a wave with halo duty issues both nodes' loads
+        // before it waits, one memory latency instead of two; lanes without a
+        // node issue none (compact levels on the 128 x 128 x 512 box 529 us with
+        // the nodes in turn, 471 so; on the 128^3 droplet 136 and 128, and 137
+        // where the idle lanes repeat their neighbour's loads)
+        FPull<ST, IN> vo, vh;
+        Coord co{};
+        if (active) co = issue(gx, gy, vo);
+        Coord ch{};
+        if (duty_lane) ch = issue(hx, hy, vh);
+        __builtin_amdgcn_sched_barrier(0);       // both nodes' loads issued before the first use
+        fpull_finish<ST, IN, MV>(a, C, co, wr, oi, vo, s);
+        if (active) put(s, oi);
+        if (duty_lane) {
+            NodeState hs;
+            fpull_finish<ST, IN, MV>(a, C, ch, wr, hi, vh, hs);
+            put(hs, hi);
         }
     } else {
-        // 16-bit forms and compact levels: the own node, then the halo node;
-        // fewer registers (3 waves per SIMD for the 16-bit pairs), measured
-        // faster for these forms
-        float qs;
-        if (active) {
-            const Coord co = make_coord_xyz<WL>(C, x0 + tx, y0 + ty, zp);
+        // 16-bit forms: the own node, then the halo node; fewer registers (3
+        // waves per SIMD for pairs, which spill with both nodes' loads: FP16S on
+        // the 128 x 128 x 512 box 548 us against 425).  With walls the own node is
+        // pulled by every lane, clamped into a ragged tile (439 -> 425 there);
+        // without walls the masked form is the faster one (128^3 118.5 against 123).
+        if (WL != WALLS_NONE || active) {
             FPull<ST, IN> vo;
-            fpull_issue<ST, IN, CP_DEFAULT, SO>(a, C, co, vo);
+            const Coord co = issue(gx, gy, vo);
             __builtin_amdgcn_sched_barrier(0);
-            fpull_finish<ST, IN, MV>(a, C, co, wr, ridx(tx, ty), vo, s);
-            slot[fidx(tx, ty)] = aux_value(C, s, qs);
-            if (wlo) wq[0][fidx(tx, ty)] = qs;
-            if (whi) wq[1][fidx(tx, ty)] = qs;
+            fpull_finish<ST, IN, MV>(a, C, co, wr, oi, vo, s);
+            if (active) put(s, oi);
         }
-        for (int eh = e; eh < nh; eh += FNT) {
-            int rx, ry;
-            halo_pos(eh, w, nrow, 1, ax, ay, rx, ry);
-            const int gx = (x0 + rx + 4 * C.nx) % C.nx, gy = (y0 + ry + 4 * C.ny) % C.ny;
-            const Coord ch = make_coord_xyz<WL>(C, gx, gy, zp);
+        if (duty_lane) {
             FPull<ST, IN> vh;
-            fpull_issue<ST, IN, CP_DEFAULT, SO>(a, C, ch, vh);
+            const Coord ch = issue(hx, hy, vh);
             __builtin_amdgcn_sched_barrier(0);
             NodeState hs;
-            fpull_finish<ST, IN, MV>(a, C, ch, wr, ridx(rx, ry), vh, hs);
-            slot[fidx(rx, ry)] = aux_value(C, hs, qs);
-            if (wlo) wq[0][fidx(rx, ry)] = qs;
-            if (whi) wq[1][fidx(rx, ry)] = qs;
+            fpull_finish<ST, IN, MV>(a, C, ch, wr, hi, vh, hs);
+            put(hs, hi);
         }
     }
-    if (h == 2) fused_ring2<ST, MV, WL, IN>(a, C, slot, wq, wlo, whi, zp, x0, y0, ax, ay);
 }
 
 // Ghost layer beyond the wall at side `side` (0: z = -1, 1: z = nz) over the
@@ -1260,8 +1304,9 @@ __device__ inline void stencil_lds(float4 (*ring)[FREG], int z, int tx, int ty, 
 // LV_COMPACT -> LV_COMPACT).
 // SO: levels read through one buffer resource per case (the host takes it
 // where every case's level is below 2^31 bytes).
-template <int ST, bool MV, int WL, int IN, int OUT, bool SO = false>
-__global__ __launch_bounds__(FNT) void k_fused(FusedArgs fa)
+// CPS: cache policy of the stored level (lbcg_init chooses by its size).
+template <int ST, bool MV, int WL, int IN, int OUT, bool SO, int CPS>
+__global__ __launch_bounds__(FNT, ST != LBCG_FP32 && IN == LV_PAIR ? 3 : 2) void k_fused(FusedArgs fa)
 {
     __shared__ float4 ring[FSLOTS][FREG];
     __shared__ float2 rring[4][RREG];
@@ -1279,50 +1324,53 @@ __global__ __launch_bounds__(FNT) void k_fused(FusedArgs fa)
         const int ax = min(FTX, C.nx - x0), ay = min(FTY, C.ny - y0);
         const bool active = tx < ax && ty < ay;
         const bool walls = WL == WALLS_Z && C.wall == 2;
+        // this lane's column, its index in the LDS planes, its halo duties
+        const int ox = min(tx, ax - 1), oy = min(ty, ay - 1), oi = fidx(ox, oy);
+        const int nh = 2 * (ax + 2) + 2 * ay, lane = (int)threadIdx.x & 63;
+        const HaloRole h0 = halo_role(C, lane, x0, y0, ax, ay), h1 = halo_role(C, 64 + lane, x0, y0, ax, ay);
         __syncthreads();                                   // both rings reused across tiles
-        // stored densities of the planes the prologue pulls read
-        for (int q = z0 - 2; q <= z0 + 1; ++q)
+        // stored densities of the planes the first pulls read
+        for (int q = z0 - 2; q <= z0; ++q)
             fused_stage_store<IN>(rring, dring, cring, q, fused_stage_load<IN>(a, C, q, x0, y0, ax, ay, walls));
         __syncthreads();
+        // From the plane below the chunk to the plane above it: the aux values of
+        // plane zn (or a ghost layer), the stored densities of plane zn + 2 for the
+        // next plane's pulls, one barrier, the collision of plane zn - 1.  The
+        // density slot written here was last read by the pulls of plane zn - 1,
+        // before the previous barrier.  (One copy of the pull code for all
+        // planes: the chunk's first two planes had copies of their own, and the
+        // kernel was 48 KB long.)
         NodeState cur, nxt;
-        // plane z0 (kept) and the plane below it (the top plane, for a
-        // periodic z at z0 = 0); at a bottom wall the ghost layer instead
-        fused_plane<ST, MV, WL, IN, SO>(a, C, ring, rring, dring, cring, wq, z0, z0, x0, y0, ax, ay,
-                                        walls && (z0 == 0 || z0 == C.nz - 1) ? 2 : 1, active, tx, ty, cur);
-        if (!(walls && z0 == 0))
-            fused_plane<ST, MV, WL, IN, SO>(a, C, ring, rring, dring, cring, wq, z0 - 1,
-                                            z0 == 0 ? C.nz - 1 : z0 - 1, x0, y0, ax, ay, 1, active, tx, ty, nxt);
-        __syncthreads();
-        fused_stage_store<IN>(rring, dring, cring, z0 + 2,
-                              fused_stage_load<IN>(a, C, z0 + 2, x0, y0, ax, ay, walls));
-        if (walls && z0 == 0) fused_ghost<MV>(C, ring, wq, 0, ax, ay);
-        __syncthreads();
-        // Each plane: the aux values of plane z + 1 (or the top ghost layer),
-        // the stored densities of plane z + 3 for the next plane's pulls, one
-        // barrier, the collision of plane z.  The density slot written here
-        // was last read by the pulls of plane z, before the previous barrier.
-        for (int z = z0; z < z1; ++z) {
-            const int zn = z + 1;
-            const RhoStage<IN> rs = fused_stage_load<IN>(a, C, z + 3, x0, y0, ax, ay, walls);
-            if (walls && zn == C.nz) {
-                fused_ghost<MV>(C, ring, wq, 1, ax, ay);
+        for (int zn = z0 - 1; zn <= z1; ++zn) {
+            RhoStage<IN> rs;
+            if (zn < z1) rs = fused_stage_load<IN>(a, C, zn + 2, x0, y0, ax, ay, walls);
+            if (walls && (zn < 0 || zn == C.nz)) {
+                if (zn > 0) fused_ghost<MV>(C, ring, wq, 1, ax, ay);
             } else {
-                const int zp = zn == C.nz ? 0 : zn;        // periodic wrap
-                fused_plane<ST, MV, WL, IN, SO>(a, C, ring, rring, dring, cring, wq, zn, zp, x0, y0, ax, ay,
-                                                walls && zp == C.nz - 1 ? 2 : 1, active, tx, ty, nxt);
+                const int zp = zn < 0 ? C.nz - 1 : (zn == C.nz ? 0 : zn);      // periodic wrap
+                if (WL == WALLS_Z && walls && (zp == 0 || zp == C.nz - 1)) {
+                    if constexpr (WL == WALLS_Z) {
+                        fused_plane<ST, MV, WL, IN, SO, true>(a, C, ring, rring, dring, cring, wq, zn, zp, x0 + ox,
+                                                              y0 + oy, active, oi, h0, h1, nh, nxt);
+                        // a wall layer's second halo ring, where its ghost layer is needed
+                        if ((zn == 0 && z0 == 0) || (zn == C.nz - 1 && z1 == C.nz))
+                            fused_ring2<ST, MV, WL, IN>(a, C, ring[fslot(zn)], wq, MV && zp == 0, MV && zp == C.nz - 1,
+                                                        zp, x0, y0, ax, ay);
+                    }
+                } else {
+                    fused_plane<ST, MV, WL, IN, SO, false>(a, C, ring, rring, dring, cring, wq, zn, zp, x0 + ox, y0 + oy,
+                                                           active, oi, h0, h1, nh, nxt);
+                }
             }
-            fused_stage_store<IN>(rring, dring, cring, z + 3, rs);
+            if (zn < z1) fused_stage_store<IN>(rring, dring, cring, zn + 2, rs);
+            // the bottom ghost layer, from plane 0 (complete since the last barrier)
+            if (walls && zn == 1 && z0 == 0) fused_ghost<MV>(C, ring, wq, 0, ax, ay);
             __syncthreads();
-            if (active) {
-                const int node = (x0 + tx) + C.nx * ((y0 + ty) + C.ny * z);
+            if (zn > z0 && active) {
+                const int z = zn - 1, node = (x0 + tx) + C.nx * ((y0 + ty) + C.ny * z);
                 Stencil st = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 stencil_lds(ring, z, tx, ty, st);
-                // FP32 levels are stored non-temporally: the level is read
-                // back only by the next step, and the caches then keep the
-                // halo pulls of neighbouring tiles (measured +10 %); the 16-bit
-                // forms measured faster with ordinary stores
-                collide_node<ST, ST == LBCG_FP32 ? CP_STREAM : CP_DEFAULT, OUT>(a, C, node, cur, st,
-                                                                               ring[fslot(z)][fidx(tx, ty)].x);
+                collide_node<ST, CPS, OUT>(a, C, node, cur, st, ring[fslot(z)][fidx(tx, ty)].x);
             }
             cur = nxt;
         }

@@ -59,6 +59,7 @@ struct lbcg_handle {
     float4 *dsc[2] = {nullptr, nullptr};
     float *crs[2] = {nullptr, nullptr};
     std::vector<uint8_t> pairlvl;      // per case: its current level is in pair format
+    bool stream_stores = false;        // the fused step stores non-temporally
     bool one_rsrc[2] = {false, false}; // per level format: every case's level fits one buffer resource
     double *partial = nullptr, *red = nullptr;
     int64_t steps = 0, total_nodes = 0, total_pop = 0, total_ghost = 0;
@@ -266,49 +267,51 @@ int for_format_runs(const lbcg_handle *h, F &&f)
     return LBCG_OK;
 }
 
-template <int ST, int IN, int OUT, bool SO>
-void launch_fused(lbcg_handle *h, hipStream_t st, const FusedArgs &fa, int grid)
+// Calls f(kernel) with the fused kernel's instance for the handle's walls.
+template <int ST, int IN, int OUT, bool SO, int CPS, class F>
+auto fused_instance(const lbcg_handle *h, F &&f)
 {
-    const dim3 g(grid), b(FTX * FTY);
-    if (h->moving) hipLaunchKernelGGL((k_fused<ST, true, WALLS_Z, IN, OUT, SO>), g, b, 0, st, fa);
-    else if (h->walls == WALLS_Z) hipLaunchKernelGGL((k_fused<ST, false, WALLS_Z, IN, OUT, SO>), g, b, 0, st, fa);
-    else hipLaunchKernelGGL((k_fused<ST, false, WALLS_NONE, IN, OUT, SO>), g, b, 0, st, fa);
+    if (h->moving) return f(k_fused<ST, true, WALLS_Z, IN, OUT, SO, CPS>);
+    if (h->walls == WALLS_Z) return f(k_fused<ST, false, WALLS_Z, IN, OUT, SO, CPS>);
+    return f(k_fused<ST, false, WALLS_NONE, IN, OUT, SO, CPS>);
 }
 
 // A step that reads and writes one level format, with every case's level
 // within one buffer resource, takes the single-resource instantiation (fewer
-// scalar registers live); the one-off pair-to-compact conversion does not.
+// scalar registers live) with the handle's store policy; the one-off
+// pair-to-compact conversion, larger levels and 16-bit compact levels do not
+// (FP32 stored non-temporally, 16-bit forms ordinarily).
+template <int ST, int IN, int OUT, class F>
+auto fused_instance(const lbcg_handle *h, F &&f)
+{
+    constexpr int CPS = ST == LBCG_FP32 ? CP_STREAM : CP_DEFAULT, OTHER = CP_STREAM - CPS;
+    if constexpr (IN == OUT) {
+        if (h->one_rsrc[IN]) {
+            if constexpr (ST == LBCG_FP32 || IN == LV_PAIR)
+                if (h->stream_stores != (CPS == CP_STREAM)) return fused_instance<ST, IN, OUT, true, OTHER>(h, f);
+            return fused_instance<ST, IN, OUT, true, CPS>(h, f);
+        }
+    }
+    return fused_instance<ST, IN, OUT, false, CPS>(h, f);
+}
+
 template <int ST, int IN, int OUT>
 void launch_fused(lbcg_handle *h, hipStream_t st, const FusedArgs &fa, int grid)
 {
-    if constexpr (IN == OUT) {
-        if (h->one_rsrc[IN]) {
-            launch_fused<ST, IN, OUT, true>(h, st, fa, grid);
-            return;
-        }
-    }
-    launch_fused<ST, IN, OUT, false>(h, st, fa, grid);
+    fused_instance<ST, IN, OUT>(h, [&](void (*k)(FusedArgs)) {
+        hipLaunchKernelGGL(k, dim3(grid), dim3(FNT), 0, st, fa);
+    });
 }
 
 // Workgroups of the handle's steady-state fused kernel that one CU holds at
 // once (its registers and LDS), as the runtime computes it; 0 on failure.
-template <int ST, int LV, bool SO>
-int fused_blocks_per_cu(const lbcg_handle *h)
-{
-    int nb = 0;
-    hipError_t e;
-    if (h->moving)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<ST, true, WALLS_Z, LV, LV, SO>, FNT, 0);
-    else if (h->walls == WALLS_Z)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<ST, false, WALLS_Z, LV, LV, SO>, FNT, 0);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fused<ST, false, WALLS_NONE, LV, LV, SO>, FNT, 0);
-    return e == hipSuccess ? nb : 0;
-}
-
 template <int ST, int LV>
 int fused_blocks_per_cu(const lbcg_handle *h)
 {
-    return h->one_rsrc[LV] ? fused_blocks_per_cu<ST, LV, true>(h) : fused_blocks_per_cu<ST, LV, false>(h);
+    return fused_instance<ST, LV, LV>(h, [](void (*k)(FusedArgs)) {
+        int nb = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, FNT, 0) == hipSuccess ? nb : 0;
+    });
 }
 
 int fused_blocks_per_cu(const lbcg_handle *h)
@@ -714,6 +717,20 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
                    ? LV_COMPACT
                    : LV_PAIR;
     h->pairlvl.assign(n_cases, 1);
+    // The fused step stores a level non-temporally where the 256 MB last-level
+    // cache would not keep it until the next step reads it: the caches then keep
+    // the halo pulls.  Below that the level is read back from the cache.  us per
+    // step, ordinary / non-temporal: FP32 96^3 (95 MB) 64.2 / 70.8, twelve impact
+    // boxes (227 MB) 165.6 / 169.9, 128^3 (226 MB) 127.7 / 126.5, 128 x 128 x 512 (906
+    // MB) 481 / 471; FP16S 64 x 64 x 256 (88 MB) 63.4 / 68.2, the twelve boxes (176 MB)
+    // 121.5 / 123.5, 128 x 128 x 512 (705 MB) 425 / 410.  Only where a tile's rows
+    // fill whole 128-byte lines (32 values of 4 bytes): a partial line stored so is
+    // not merged with its neighbour's part (sixteen impact boxes of odd sides, FP16S,
+    // 508 MB: 470 / 580).
+    h->stream_stores = h->total_nodes * (h->level == LV_COMPACT ? 20 * h->elem + 28 : 38 * h->elem + 8) >=
+                       (int64_t)240 << 20;
+    for (const DevCase &d : h->dc)
+        if (d.nx % 32) h->stream_stores = false;
     // level bytes: pairs 19 NS pairs, compact levels 20 NS values
     h->one_rsrc[LV_PAIR] = h->one_rsrc[LV_COMPACT] = true;
     for (const DevCase &d : h->dc) {
