@@ -451,10 +451,9 @@ int capture_graph(lbcg_handle *h)
     return LBCG_OK;
 }
 
-// FP64 sums over tiles [t0, t0 + nt) into h->red[0..5]; optional field exports.
-// FP64 sums over the whole cases whose tiles are [t0, t0 + nt), one launch per
-// run of cases with the same level format.
-template <int ST>
+// Field exports and (sums) FP64 sums into h->red[0..5] over the whole cases whose
+// tiles are [t0, t0 + nt), one launch per run of cases with the same level format.
+template <int ST, bool SUMS>
 int moments_impl(lbcg_handle *h, int t0, int nt, float *rR, float *rB, float *rN, float *ux, float *uy,
                  float *uz)
 {
@@ -465,32 +464,34 @@ int moments_impl(lbcg_handle *h, int t0, int nt, float *rR, float *rB, float *rN
         if (r1 <= r0) return (int)LBCG_OK;
         double *part = h->partial + (size_t)6 * (r0 - t0);
         if (fmt == LV_COMPACT)
-            hipLaunchKernelGGL((k_moments<ST, LV_COMPACT>), dim3(r1 - r0), dim3(h->block), 0, h->stream, a, r0, rR,
+            hipLaunchKernelGGL((k_moments<ST, LV_COMPACT, SUMS>), dim3(r1 - r0), dim3(h->block), 0, h->stream, a, r0, rR,
                                rB, rN, ux, uy, uz, part);
         else
-            hipLaunchKernelGGL((k_moments<ST, LV_PAIR>), dim3(r1 - r0), dim3(h->block), 0, h->stream, a, r0, rR,
+            hipLaunchKernelGGL((k_moments<ST, LV_PAIR, SUMS>), dim3(r1 - r0), dim3(h->block), 0, h->stream, a, r0, rR,
                                rB, rN, ux, uy, uz, part);
         return (int)LBCG_OK;
     });
     if (rc) return rc;
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, h->stream, (const double *)h->partial, nt, h->red);
+    if constexpr (SUMS)
+        hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, h->stream, (const double *)h->partial, nt, h->red);
     HIPCHK(hipGetLastError());
     return LBCG_OK;
 }
 
+template <bool SUMS>
 int moments_any(lbcg_handle *h, int t0, int nt, float *rR, float *rB, float *rN, float *ux, float *uy,
                 float *uz)
 {
     switch (h->storage) {
-    case LBCG_FP32: return moments_impl<LBCG_FP32>(h, t0, nt, rR, rB, rN, ux, uy, uz);
-    case LBCG_FP16S: return moments_impl<LBCG_FP16S>(h, t0, nt, rR, rB, rN, ux, uy, uz);
-    default: return moments_impl<LBCG_BF16S>(h, t0, nt, rR, rB, rN, ux, uy, uz);
+    case LBCG_FP32: return moments_impl<LBCG_FP32, SUMS>(h, t0, nt, rR, rB, rN, ux, uy, uz);
+    case LBCG_FP16S: return moments_impl<LBCG_FP16S, SUMS>(h, t0, nt, rR, rB, rN, ux, uy, uz);
+    default: return moments_impl<LBCG_BF16S, SUMS>(h, t0, nt, rR, rB, rN, ux, uy, uz);
     }
 }
 
 int stability_check(lbcg_handle *h)
 {
-    int rc = moments_any(h, 0, h->ntiles, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    int rc = moments_any<true>(h, 0, h->ntiles, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     if (rc) return rc;
     double out[6];
     HIPCHK(hipMemcpyAsync(out, h->red, sizeof out, hipMemcpyDeviceToHost, h->stream));
@@ -929,7 +930,9 @@ int lbcg_moments(lbcg_handle *h, int32_t case_id, float *rhoR, float *rhoB, floa
     int rc = check_handle(h);
     if (rc) return rc;
     if (case_id < 0 || case_id >= h->ncases) return fail(LBCG_EINVAL, "case_id out of range");
-    rc = moments_any(h, h->tile_begin[case_id], h->tile_count[case_id], rhoR, rhoB, rhoN, ux, uy, uz);
+    const int t0 = h->tile_begin[case_id], nt = h->tile_count[case_id];
+    rc = diag ? moments_any<true>(h, t0, nt, rhoR, rhoB, rhoN, ux, uy, uz)
+              : moments_any<false>(h, t0, nt, rhoR, rhoB, rhoN, ux, uy, uz);
     if (rc) return rc;
     if (diag) {
         double out[6];
