@@ -143,8 +143,7 @@ typedef struct lbcg_fields {
  * all cases together are at most two 16 x 4 x 4 bricks per CU, the single-pass
  * step advances bricks (zchunk 4) instead of marching tiles; so does an FP32
  * handle whose walls on x or y make LBCG_KERNEL_AUTO take the two-pass step, up
- * to one brick per CU (two with moving walls), if block_nodes and
- * persistent_blocks are 0 too.  The results agree to FP32 rounding.
+ * to one brick per CU, if block_nodes and persistent_blocks are 0 too.  The results agree to FP32 rounding.
  * graph_steps: 0 = launch every kernel of every step; n > 0 = capture n steps
  * (rounded up to even) once into a HIP graph and replay it; with diag_every
  * the stability check then runs at the first replay boundary at or after each

@@ -191,54 +191,63 @@ struct NodeState {
 template <int I>
 constexpr int pair_first() { return I == 0 ? 0 : ((I & 1) ? I : I - 1); }
 
-// MV: the launch holds a case with a moving wall (a separate instantiation, so
-// that cases at rest pay nothing for the wall-gain code).
-template <int ST, bool MV, int CPP, int I>
-__device__ inline void pull_one(const StepArgs &a, DC &C, const Coord &c, const float2 own,
-                                NodeState &s, float &eR, float &eB)
-{
-    using S = Storage<ST>;
-    using P = typename S::P;
-    constexpr int F = pair_first<I>(), W = I == 0 ? 1 : 2;
-    const size_t N = (size_t)C.N, NS = (size_t)C.NS;
-    const P *base = reinterpret_cast<const P *>(a.fin) + C.pop_off / 2;
-    const bool bb = bounce<I>(c);
-    const uint32_t si = (uint32_t)(bb ? c.node : neighbour<-ex(I), -ey(I), -ez(I)>(c));
-    constexpr bool hi_own = I != F, hi_opp = opp(I) != F;          // second array of the pair?
-    const bool hi = bb ? hi_opp : hi_own;
-    const uint32_t e = si + (hi ? (uint32_t)NS : 0u);
-    const P v = buf_ld<P, CPP>(rsrc(base + (size_t)F * NS, W * NS * sizeof(P)), e * (uint32_t)sizeof(P));
-    const float dR = S::dec(v.r, a.inv_scale);
-    const float dB = S::dec(v.b, a.inv_scale);
-    const float2 ps = buf_ld<float2, CP_DEFAULT>(rsrc(a.rho_prev + C.node_off, N * sizeof(float2)), si * 8u);
-    float tR = __builtin_fmaf(ps.x - own.x, C.phi[0][ecls(I)], dR);
-    float tB = __builtin_fmaf(ps.y - own.y, C.phi[1][ecls(I)], dB);
-    if constexpr (MV && I != 0) {
-        if (C.moving && bb) {        // moving wall: the reflected population gains its momentum
-            const float eu = wall_eu<I>(C, bounce_side<I>(c));
-            tR = __builtin_fmaf(eu * C.wg[0][ecls(I) - 1], own.x, tR);
-            tB = __builtin_fmaf(eu * C.wg[1][ecls(I) - 1], own.y, tB);
-        }
-    }
-    const float h = tR + tB;
-    s.h[I] = h;
-    eR += tR;
-    eB += tB;
-    if constexpr (ex(I) == 1) s.jx += h;
-    if constexpr (ex(I) == -1) s.jx -= h;
-    if constexpr (ey(I) == 1) s.jy += h;
-    if constexpr (ey(I) == -1) s.jy -= h;
-    if constexpr (ez(I) == 1) s.jz += h;
-    if constexpr (ez(I) == -1) s.jz -= h;
-}
-
-template <int ST, bool MV, int CPP, int I = 0>
-__device__ inline void pull_all(const StepArgs &a, DC &C, const Coord &c, const float2 own,
-                                NodeState &s, float &eR, float &eB)
+// The loads of a pull in the two-pass step: direction I's population pair and
+// its writer's densities.  All 38 are issued before the first use: the compiler
+// kept about seven in flight, and a small box waits for memory, not for bandwidth
+// (plates on 140 x 140 x 4 nodes, moving walls: 40 us per step, 35 so, and 22 with no
+// array indexed by the wall axis, which the compiler keeps in LDS or scratch).
+template <int ST, int CPP, int I = 0>
+__device__ inline void pull_load(const StepArgs &a, DC &C, const Coord &c, typename Storage<ST>::P (&v)[Q],
+                                 float2 (&ps)[Q])
 {
     if constexpr (I < Q) {
-        pull_one<ST, MV, CPP, I>(a, C, c, own, s, eR, eB);
-        pull_all<ST, MV, CPP, I + 1>(a, C, c, own, s, eR, eB);
+        using P = typename Storage<ST>::P;
+        constexpr int F = pair_first<I>(), W = I == 0 ? 1 : 2;
+        const size_t N = (size_t)C.N, NS = (size_t)C.NS;
+        const P *base = reinterpret_cast<const P *>(a.fin) + C.pop_off / 2;
+        const bool bb = bounce<I>(c);
+        const uint32_t si = (uint32_t)(bb ? c.node : neighbour<-ex(I), -ey(I), -ez(I)>(c));
+        constexpr bool hi_own = I != F, hi_opp = opp(I) != F;      // second array of the pair?
+        const bool hi = bb ? hi_opp : hi_own;
+        const uint32_t e = si + (hi ? (uint32_t)NS : 0u);
+        v[I] = buf_ld<P, CPP>(rsrc(base + (size_t)F * NS, W * NS * sizeof(P)), e * (uint32_t)sizeof(P));
+        ps[I] = buf_ld<float2, CP_DEFAULT>(rsrc(a.rho_prev + C.node_off, N * sizeof(float2)), si * 8u);
+        pull_load<ST, CPP, I + 1>(a, C, c, v, ps);
+    }
+}
+
+// MV: the launch holds a case with a moving wall (a separate instantiation, so
+// that cases at rest pay nothing for the wall-gain code).
+template <int ST, bool MV, int I = 0>
+__device__ inline void pull_all(const StepArgs &a, DC &C, const Coord &c, const float2 own,
+                                const typename Storage<ST>::P (&v)[Q], const float2 (&ps)[Q], NodeState &s, float &eR,
+                                float &eB)
+{
+    if constexpr (I < Q) {
+        using S = Storage<ST>;
+        const bool bb = bounce<I>(c);
+        const float dR = S::dec(v[I].r, a.inv_scale);
+        const float dB = S::dec(v[I].b, a.inv_scale);
+        float tR = __builtin_fmaf(ps[I].x - own.x, C.phi[0][ecls(I)], dR);
+        float tB = __builtin_fmaf(ps[I].y - own.y, C.phi[1][ecls(I)], dB);
+        if constexpr (MV && I != 0) {
+            if (C.moving && bb) {        // moving wall: the reflected population gains its momentum
+                const float eu = wall_eu<I>(C, bounce_side<I>(c));
+                tR = __builtin_fmaf(eu * C.wg[0][ecls(I) - 1], own.x, tR);
+                tB = __builtin_fmaf(eu * C.wg[1][ecls(I) - 1], own.y, tB);
+            }
+        }
+        const float h = tR + tB;
+        s.h[I] = h;
+        eR += tR;
+        eB += tB;
+        if constexpr (ex(I) == 1) s.jx += h;
+        if constexpr (ex(I) == -1) s.jx -= h;
+        if constexpr (ey(I) == 1) s.jy += h;
+        if constexpr (ey(I) == -1) s.jy -= h;
+        if constexpr (ez(I) == 1) s.jz += h;
+        if constexpr (ez(I) == -1) s.jz -= h;
+        pull_all<ST, MV, I + 1>(a, C, c, own, v, ps, s, eR, eB);
     }
 }
 
@@ -528,9 +537,13 @@ __device__ inline void pull_node(const StepArgs &a, DC &C, const Coord &c, NodeS
 {
     const float2 own = buf_ld<float2, CP_DEFAULT>(rsrc(a.rho_prev + C.node_off, (size_t)C.N * sizeof(float2)),
                                                   (uint32_t)c.node * 8u);
+    typename Storage<ST>::P v[Q];
+    float2 ps[Q];
+    pull_load<ST, CPP>(a, C, c, v, ps);
+    __builtin_amdgcn_sched_barrier(0);           // every load in flight before the first use
     float eR = 0.f, eB = 0.f;
     s.jx = s.jy = s.jz = 0.f;
-    pull_all<ST, MV, CPP>(a, C, c, own, s, eR, eB);
+    pull_all<ST, MV>(a, C, c, own, v, ps, s, eR, eB);
     s.R[0] = own.x + eR;
     s.R[1] = own.y + eB;
     s.D[0] = s.R[0] - own.x;
@@ -581,14 +594,12 @@ __global__ __launch_bounds__(256) void k_aux(StepArgs a)
         const Macro m = macro(C, s);
         const float qs = s.R[0] * C.qc[0] + s.R[1] * C.qc[1];
         a.aux[C.node_off + node] = make_float4(phase_field(C, s.R[0], s.R[1]), m.ux * qs, m.uy * qs, m.uz * qs);
-        if (MV && C.moving && (c.lo[C.wall] || c.hi[C.wall])) {
+        if (MV && C.moving && (c.lo[0] || c.hi[0] || c.lo[1] || c.hi[1] || c.lo[2] || c.hi[2])) {
             // first-layer density factor of Qbar for the ghost layer of a moving wall
-            const int w = C.wall, b = w == 0 ? 1 : 0, cax = w == 2 ? 1 : 2;
-            const int co[3] = {c.x, c.y, c.z};
-            const int n[3] = {C.nx, C.ny, C.nz};
-            const int pi = co[b] + n[b] * co[cax];
-            if (c.lo[w]) a.wallq[C.ghost_off + pi] = qs;
-            if (c.hi[w]) a.wallq[C.ghost_off + C.plane + pi] = qs;
+            const int w = C.wall;
+            const int pi = w == 0 ? c.y + C.ny * c.z : c.x + C.nx * (w == 1 ? c.z : c.y);
+            if (w == 0 ? c.lo[0] : (w == 1 ? c.lo[1] : c.lo[2])) a.wallq[C.ghost_off + pi] = qs;
+            if (w == 0 ? c.hi[0] : (w == 1 ? c.hi[1] : c.hi[2])) a.wallq[C.ghost_off + C.plane + pi] = qs;
         }
     }
 }
@@ -608,11 +619,14 @@ __global__ __launch_bounds__(256) void k_ghost(StepArgs a, const int2 *gtiles, i
         if (e >= 2 * C.plane) continue;
         const int side = e >= C.plane ? 1 : 0;
         const int pi = e - side * C.plane;
-        int n[3] = {C.nx, C.ny, C.nz};
-        const int w = C.wall, b = w == 0 ? 1 : 0, cax = w == 2 ? 1 : 2;
-        const int ib = pi % n[b], ic = pi / n[b];
-        int q[3];
-        q[w] = side ? n[w] - 1 : 0;
+        // extents and strides of the wall axis and of the plane's axes (no arrays
+        // indexed by the axis: those would live in memory)
+        const int w = C.wall, nxy = C.nx * C.ny;
+        const int nw = w == 0 ? C.nx : (w == 1 ? C.ny : C.nz), sw = w == 0 ? 1 : (w == 1 ? C.nx : nxy);
+        const int nb = w == 0 ? C.ny : C.nx, sb = w == 0 ? C.nx : 1;
+        const int nc = w == 2 ? C.ny : C.nz, sc = w == 2 ? C.nx : nxy;
+        const int ib = pi % nb, ic = pi / nb;
+        const float4 *layer = a.aux + C.node_off + (side ? nw - 1 : 0) * sw;
         float gb = 0.f, gc = 0.f;
         #pragma unroll
         for (int db = -1; db <= 1; ++db) {
@@ -621,16 +635,14 @@ __global__ __launch_bounds__(256) void k_ghost(StepArgs a, const int2 *gtiles, i
                 if (db == 0 && dc == 0) continue;
                 const float wgt = (db != 0 && dc != 0) ? (1.0f / 12.0f) : (1.0f / 3.0f);
                 int vb = ib + db, vc = ic + dc;
-                vb = vb < 0 ? n[b] - 1 : (vb >= n[b] ? 0 : vb);
-                vc = vc < 0 ? n[cax] - 1 : (vc >= n[cax] ? 0 : vc);
-                q[b] = vb; q[cax] = vc;
-                const float v = a.aux[C.node_off + q[0] + C.nx * (q[1] + C.ny * q[2])].x;
+                vb = vb < 0 ? nb - 1 : (vb >= nb ? 0 : vb);
+                vc = vc < 0 ? nc - 1 : (vc >= nc ? 0 : vc);
+                const float v = layer[vb * sb + vc * sc].x;
                 gb += wgt * (float)db * v;
                 gc += wgt * (float)dc * v;
             }
         }
-        q[b] = ib; q[cax] = ic;
-        const float4 s = a.aux[C.node_off + q[0] + C.nx * (q[1] + C.ny * q[2])];
+        const float4 s = layer[ib * sb + ic * sc];
         const float gpar = sqrtf(gb * gb + gc * gc);
         // Qbar takes the wall's value half way: ghost = 2 Qbar(wall) - Qbar(first
         // layer), Qbar(wall) = U_w sum_k rho_k (1 - 3 c_s^k^2) of the first layer

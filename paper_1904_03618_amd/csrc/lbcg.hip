@@ -757,14 +757,14 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     // 23.5 / 29.0 / 19.0, 64^3 (1024) 43.0 / 32.3 / 34.0; FP16S at 48^3 23.0 /
     // 24.6, at 64^3 41.9 / 28.5.  A handle that has to take the two-pass step
     // (walls on x or y, pair levels) saves two launches with one brick per CU
-    // (13.9 + 4.6 us against 12), with moving walls, whose passes are longer, with
-    // two (the plates on 140 x 140 x 4 nodes, 315 bricks: 40 -> 22; at rest 42 x
-    // 69 x 20, 270 bricks, 18.7 against 25.5), in FP32: in the 16-bit forms the
-    // passes' last-bit rounding would change the stored values.
+    // (plates on 64 x 64 x 4 nodes 15.4 us in passes, 12 in bricks; beyond it 42 x
+    // 69 x 20, 270 bricks, 17.9 against 25.5, plates on 140 x 140 x 4, 315 bricks, 21.9
+    // against 22.6), in FP32: in the 16-bit forms the passes' last-bit rounding
+    // would change the stored values.
     const int64_t bricks = ntiles_of(KX, KY, KZ);
     const bool single = h->fused && bricks <= 2 * (int64_t)ncu;
     const bool instead = !h->fused && o.kernel == LBCG_KERNEL_AUTO && opt_block == 0 && o.persistent_blocks == 0 &&
-                         o.storage == LBCG_FP32 && bricks <= (h->moving ? 2 : 1) * (int64_t)ncu;
+                         o.storage == LBCG_FP32 && bricks <= (int64_t)ncu;
     h->brick = dev_ok && o.zchunk == 0 && (single || instead) && h->one_rsrc[h->level] &&
                (h->level == LV_PAIR || o.storage == LBCG_FP32);
     h->zc = o.zchunk;
