@@ -211,7 +211,7 @@ __device__ inline void store_out(const sg_view &y, const sg_view &y32, int64_t p
         for (int j = 0; j < 4; ++j) v[j] = fmaxf(v[j], 0.f);
     if (y.p) {
         bf16 *out = reinterpret_cast<bf16 *>(y.p) + pb * y.ctot + y.coff + oc0;
-        if (((y.ctot | y.coff) & 3) == 0 && oc0 + 3 < y.c) {
+        if (((y.ctot | y.coff) & 3) == 0 && ((uintptr_t)y.p & 7) == 0 && oc0 + 3 < y.c) {
             *reinterpret_cast<bf16x4 *>(out) = bf16x4{(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
         } else {
             #pragma unroll
@@ -221,7 +221,7 @@ __device__ inline void store_out(const sg_view &y, const sg_view &y32, int64_t p
     }
     if (y32.p) {
         float *out = reinterpret_cast<float *>(y32.p) + pb * y32.ctot + y32.coff + oc0;
-        if (((y32.ctot | y32.coff) & 3) == 0 && oc0 + 3 < y32.c) {
+        if (((y32.ctot | y32.coff) & 3) == 0 && ((uintptr_t)y32.p & 15) == 0 && oc0 + 3 < y32.c) {
             f32x4 *o4 = reinterpret_cast<f32x4 *>(out);
             *o4 = accumulate ? *o4 + v : v;
         } else {

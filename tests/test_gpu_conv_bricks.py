@@ -117,3 +117,23 @@ def test_pointwise_weight_gradient(shape, ci, co):
     ok, err = close(layer.gw.cpu().numpy(), dW)
     ok2, err2 = close(layer.gb.cpu().numpy(), db)
     assert ok and ok2, (err, err2)
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 4, 16), (1, 3, 5, 9)])
+def test_outputs_that_start_off_a_vector_boundary(shape):
+    """Output tensors aligned to one value only: the same results as aligned
+    ones, bit for bit, and nothing written beside them."""
+    import torch
+    from paper_1904_03618_amd import surrogate as S
+    rng = np.random.default_rng(shape)
+    layer, _, _ = _layer(16, 16, rng)
+    xt, _ = bft(rng.standard_normal(shape + (16,)))
+    n = int(np.prod(shape)) * 16
+    y, y32 = (torch.zeros(shape + (16,), dtype=d, device="cuda") for d in (torch.bfloat16, torch.float32))
+    layer.fwd(S.view(xt), S.view(y), S.view(y32), pmask=3)
+    bufs = [torch.full((n + 16,), 7.0, dtype=t.dtype, device="cuda") for t in (y, y32)]
+    oy, o32 = (b[1:1 + n].view(shape + (16,)) for b in bufs)
+    layer.fwd(S.view(xt), S.view(oy), S.view(o32), pmask=3)
+    assert torch.equal(oy, y) and torch.equal(o32, y32)
+    for b in bufs:
+        assert float(b[0]) == 7.0 and bool((b[1 + n:] == 7.0).all())
