@@ -2,7 +2,8 @@
 // colour-gradient MRT lattice Boltzmann model (Wen, Li, Yu & Luo).
 //
 // A step at level t is either one launch of k_fused (below: z-marching
-// tiles, the phase-field halo in LDS; cases with walls, if any, on z), or the
+// tiles, the phase-field halo in LDS; cases with walls, if any, on z) or of
+// k_brick (small boxes, one brick of nodes per workgroup), or the
 // two-pass form, three launches over all tiles of all cases:
 //   k_aux     pull the 38 populations, moments (Eq. 4), phase field rho^N
 //             (text after Eq. 8) and Qbar = u sum_k rho_k (1 - 3 c_s^k^2)
