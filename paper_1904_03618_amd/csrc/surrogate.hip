@@ -904,11 +904,14 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, in
 
 // Fixed-order sum of the per-group partials of the weights (n values, group
 // stride gs) and the bias (nb values, group stride gsb): 32 outputs x 8 slices of
-// the groups per workgroup, the slices added in order through LDS.
+// the groups per workgroup, the slices added in order through LDS.  A chain of
+// load latencies: U of them in flight where a slice has that many groups (16 ->
+// 16 channels on 4 x 64^3 positions, 768 groups: 15.6 -> 12 us).
 __global__ __launch_bounds__(256) void k_reduce_groups(const float *__restrict__ ws, int64_t gs, int64_t n,
                                                        const float *__restrict__ wsb, int gsb, int nb, int groups,
                                                        float *dw, float *db)
 {
+    constexpr int U = 16;
     __shared__ float sh[8][32];
     const int l = threadIdx.x & 31, s = threadIdx.x >> 5;
     const int64_t e = (int64_t)blockIdx.x * 32 + l;
@@ -917,8 +920,17 @@ __global__ __launch_bounds__(256) void k_reduce_groups(const float *__restrict__
     const int64_t st = bias ? gsb : gs;
     float acc = 0.f;
     if (e < n + nb) {
+        int g = s;
+        for (; g + 8 * (U - 1) < groups; g += 8 * U) {     // U loads in flight, added in order
+            float v[U];
+            #pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = src[(g + 8 * u) * st];
+            __builtin_amdgcn_sched_barrier(0);
+            #pragma unroll
+            for (int u = 0; u < U; ++u) acc += v[u];
+        }
         #pragma unroll 4
-        for (int g = s; g < groups; g += 8) acc += src[g * st];
+        for (; g < groups; g += 8) acc += src[g * st];
     }
     sh[s][l] = acc;
     __syncthreads();
