@@ -125,13 +125,13 @@ class Conv:
         split = lambda t: (t[:n].view(self.co, self.K), t[n:n + self.co])
         (self.w, self.b), (self.gw, self.gb) = split(par), split(grad)
         (self.mw, self.mb), (self.vw, self.vb) = split(m), split(v)
-        self.bias_pad, self.placed = par[n:], (self.w, self.b, self.gw, self.gb, self.mw, self.vw, self.mb, self.vb)
+        self.bias_pad = par[n:]
 
     def prep(self):
         _chk(lib().sg_weight_prep(C.c_void_p(self.w.data_ptr()), self.co, self.ci, self.k,
                                   C.c_void_p(self.wb.data_ptr()), C.c_void_p(self.wt.data_ptr()),
                                   self.co_pad, self.ci_pad, _stream()), "sg_weight_prep")
-        if self.b is not self.placed[1]:              # a bias the caller put in the layer's place
+        if self.b.data_ptr() != self.bias_pad.data_ptr():     # the bias is not (or no longer) a view of bias_pad
             self.bias_pad[: self.co].copy_(self.b)
 
     def params(self):
@@ -284,12 +284,27 @@ class UNet:
         _chk(lib().sg_mse(C.byref(view(self.out32)), C.byref(view(self.tgt32)), C.byref(view(self.g["out32"])),
                           C.c_void_p(self.loss.data_ptr()), _stream()), "mse")
 
+    def _in_flat(self):
+        """Whether the layers' arrays still fill self.flat as __init__ placed them.
+        By address: a tensor object can outlive its place in the flat arrays
+        (pickle gives every tensor memory of its own, as does `layer.w.data = t`)."""
+        if not self.flat.is_contiguous():
+            return False
+        base, at = [f.data_ptr() for f in self.flat], 0
+        for l in self.layers:
+            for (w, g, m, v), n in zip(l.params(), (l.co * l.K, l.co)):
+                if any(t.data_ptr() != p + 4 * at or t.numel() != n for t, p in zip((w, g, m, v), base)):
+                    return False
+                at += n
+            at += l.co_pad - l.co
+        return at == self.flat.shape[1]
+
     def adam(self, lr, b1=0.9, b2=0.999, eps=1e-8):
         self.step_count += 1
-        if all(a is b for l in self.layers
-               for a, b in zip((l.w, l.b, l.gw, l.gb, l.mw, l.vw, l.mb, l.vb), l.placed)):
+        # (eps > 0 leaves the padding of the biases at zero)
+        if eps > 0 and self._in_flat():
             groups = [tuple(self.flat)]
-        else:                                         # the caller gave a layer tensors of its own
+        else:                                         # a layer has tensors of its own
             groups = [p for l in self.layers for p in l.params()]
         for w, g, m, v in groups:
             _chk(lib().sg_adam(C.c_void_p(w.data_ptr()), C.c_void_p(g.data_ptr()), C.c_void_p(m.data_ptr()),
