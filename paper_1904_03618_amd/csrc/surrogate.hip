@@ -675,8 +675,12 @@ __global__ void k_weight_prep(const float *w32, int co, int ci, int k, bf16 *wb,
 // Wave w owns taps w, w + 4, ...; its accumulators stay in registers over all
 // bricks of its group (a contiguous run), the next brick's loads are issued
 // before the current brick's MFMAs, and each group writes one partial sum per
-// weight to ws[group][co_pad][K].  Extents need not be multiples of the brick:
-// positions beyond the box carry dy = 0.
+// weight to ws[group][co_pad][K].  Extents need not be multiples of the brick
+// (RAG): planes beyond the box are skipped; positions beyond it in x or y carry
+// dy = 0, and their x rows are read from a block of zeros, since a tap reaches
+// back into the box from there and 0 x Inf would enter a sum that the value is
+// no part of (16 -> 16 channels on 61 x 67 x 71 positions 22.9 us without, 25.2 so;
+// clearing the fragments instead 25.0 there, but 64 -> 64 146 against 127).
 constexpr int WP = 256;              // positions per brick
 constexpr int WTAPS = 7;             // taps per wave (27 taps over 4 waves)
 
@@ -696,8 +700,8 @@ __device__ inline bf16x8 read_tr(const bf16 *r0, const bf16 *r1)
 // NOB x NCB blocks of 16 output x 16 input channels per workgroup; BX x BY x
 // BZ = 256 positions per brick (27 taps); K1: a 1x1x1 layer, whose bricks are
 // 256 consecutive positions and whose waves share the K blocks.
-template <int NOB, int NCB, int BX, int BY, int BZ, bool K1>
-__global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, int pmask, int co_pad, int nbx, int nby,
+template <int NOB, int NCB, int BX, int BY, int BZ, bool K1, bool RAG>
+__global__ __launch_bounds__(256, NOB * NCB == 1 ? 3 : 2) void k_conv_bwd_w(sg_view x, sg_view dy, int pmask, int co_pad, int nbx, int nby,
                                                     int nbz, int64_t nbricks, float *ws, float *wsb)
 {
     static_assert(BX * BY * BZ == WP && 16 % BX == 0, "brick shape");
@@ -707,6 +711,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, in
     constexpr int NT = K1 ? 1 : WTAPS;
     __shared__ __attribute__((aligned(16))) bf16 xs[NCB][HPW][16];
     __shared__ __attribute__((aligned(16))) bf16 dys[NOB][WP][16];
+    static_assert(!RAG || !K1, "1x1x1 layers have no position beyond the last");
+    constexpr int ZE = RAG ? 16 * (2 + HXW * (2 + HYW * 2)) + 8 : 8;     // a row of zeros at every tap's offset
+    __shared__ __attribute__((aligned(16))) bf16 zeros[ZE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, grp = lane >> 4;
     const int ci = x.c, taps = K1 ? 1 : 27, K = taps * ci;
@@ -811,6 +818,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, in
         to[i] = K1 ? 0 : 16 * (t % 3 + HXW * ((t / 3) % 3 + HYW * (t / 9)));
     }
 
+    if constexpr (RAG)
+        for (int e = 8 * tid; e < ZE; e += 8 * 256) *reinterpret_cast<bf16x8 *>(&zeros[e]) = zero;
+
     const int64_t b0 = nbricks * blockIdx.x / gridDim.x, b1 = nbricks * (blockIdx.x + 1) / gridDim.x;
     if (b0 < b1) load(b0);
     for (int64_t b = b0; b < b1; ++b) {
@@ -819,6 +829,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, in
         __syncthreads();
         // planes of this brick inside the box (K blocks beyond it are skipped)
         const int nz = K1 ? BZ : min(BZ, x.d - (int)(b / ((int64_t)nbx * nby) % nbz) * BZ);
+        // positions of this lane's rows inside the box in x; the row of its first position
+        const bool in_x = (int)(b % nbx) * BX + lp % BX < x.w;
+        const int Y0 = (int)(b / nbx % nby) * BY;
         if (b + 1 < b1) load(b + 1);
         #pragma unroll
         for (int ks = 0; ks < WP / 32; ++ks) {
@@ -830,13 +843,23 @@ __global__ __launch_bounds__(256, 2) void k_conv_bwd_w(sg_view x, sg_view dy, in
             #pragma unroll
             for (int o = 0; o < NOB; ++o)
                 a[o] = read_tr(&dys[o][32 * ks + lp][lc], &dys[o][32 * ks + 16 + lp][lc]);
+            // the lane's rows (a position, 4 channels) at the first tap
+            const bf16 *r0[NCB], *r1[NCB];
+            #pragma unroll
+            for (int c = 0; c < NCB; ++c) {
+                r0[c] = &xs[c][0][0] + hk + xo0;
+                r1[c] = &xs[c][0][0] + hk + xo1;
+                if constexpr (RAG) {
+                    if (!in_x || Y0 + (32 * ks + lp) / BX % BY >= x.h) r0[c] = zeros;
+                    if (!in_x || Y0 + (32 * ks + 16 + lp) / BX % BY >= x.h) r1[c] = zeros;
+                }
+            }
             #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 if (!K1 && i == NT - 1 && wave == 3) continue;     // 27 taps: wave 3 has six
                 #pragma unroll
                 for (int c = 0; c < NCB; ++c) {
-                    const bf16 *xc = &xs[c][0][0] + hk + to[i];
-                    const bf16x8 bb = read_tr(xc + xo0, xc + xo1);
+                    const bf16x8 bb = read_tr(r0[c] + to[i], r1[c] + to[i]);
                     #pragma unroll
                     for (int o = 0; o < NOB; ++o) acc[i][o][c] = mfma(a[o], bb, acc[i][o][c]);
                 }
@@ -1395,8 +1418,13 @@ static void bwd_launch(const sg_view *x, const sg_view *dy, int pmask, float *dw
     int64_t g = std::min<int64_t>(nb, std::max<int64_t>(1, target / ((int64_t)gy * gz)));
     g = std::min<int64_t>(g, b.max_groups);
     float *wsb = db ? ws + b.bias_off : nullptr;
-    hipLaunchKernelGGL((k_conv_bwd_w<NOB, NCB, BX, BY, BZ, K1>), dim3((unsigned)g, gy, gz), dim3(256), 0, st, *x, *dy,
-                       pmask, b.co_pad, nbx, nby, nbz, nb, ws, wsb);
+    const dim3 grid((unsigned)g, gy, gz);
+    if (!K1 && (x->w % BX || x->h % BY))
+        hipLaunchKernelGGL((k_conv_bwd_w<NOB, NCB, BX, BY, BZ, K1, !K1>), grid, dim3(256), 0, st, *x, *dy, pmask,
+                           b.co_pad, nbx, nby, nbz, nb, ws, wsb);
+    else
+        hipLaunchKernelGGL((k_conv_bwd_w<NOB, NCB, BX, BY, BZ, K1, false>), grid, dim3(256), 0, st, *x, *dy, pmask,
+                           b.co_pad, nbx, nby, nbz, nb, ws, wsb);
     const int64_t n = (int64_t)dy->c * b.K;
     const int nbias = db ? dy->c : 0;
     hipLaunchKernelGGL(k_reduce_groups, dim3((unsigned)((n + nbias + 31) / 32)), dim3(256), 0, st, (const float *)ws,
