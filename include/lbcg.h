@@ -140,10 +140,9 @@ typedef struct lbcg_fields {
  * chunk in 1 .. 128 planes (FP32) or 1 .. 64 (16-bit forms) that minimises
  * ceil(T / S) (zc + 2), the longer on a tie, or the longest where that one
  * gives T >= 2 S; lbcg_zchunk reports it).  Small boxes: where zchunk is 0 and
- * all cases together are at most two 16 x 4 x 4 bricks per CU, the single-pass
- * step advances bricks (zchunk 4) instead of marching tiles; so does an FP32
- * handle whose walls on x or y make LBCG_KERNEL_AUTO take the two-pass step, up
- * to one brick per CU, if block_nodes and persistent_blocks are 0 too.  The results agree to FP32 rounding.
+ * all cases together are at most two 16 x 4 x 4 bricks per CU, the fused step
+ * advances bricks instead of marching tiles (lbcg_zchunk reports 4; FP32, and
+ * the 16-bit forms with pair levels).
  * graph_steps: 0 = launch every kernel of every step; n > 0 = capture n steps
  * (rounded up to even) once into a HIP graph and replay it; with diag_every
  * the stability check then runs at the first replay boundary at or after each
@@ -241,7 +240,7 @@ int lbcg_get_populations(lbcg_handle *h, int32_t case_id, float *f);
  * recording an event pair around every kernel of every following step
  * (enable = 0 stops).  lbcg_timing_read synchronises the stream and writes,
  * for the kernels {moments pass, wall ghost layer, collision pass, fused
- * step} (a handle on the fused step, or on bricks, records only the last), the summed duration in milliseconds into ms[4] and the number of
+ * step} (a handle on the fused step records only the last), the summed duration in milliseconds into ms[4] and the number of
  * recorded launches into launches[4]; it then clears the totals.  Errors: LBCG_ESTATE,
  * LBCG_EINVAL (NULL output), LBCG_EDEVICE. */
 int lbcg_timing(lbcg_handle *h, int32_t enable);

@@ -1399,9 +1399,9 @@ __global__ __launch_bounds__(FNT, ST != LBCG_FP32 && IN == LV_PAIR ? 3 : 2) void
 // barrier and one collision long whatever the box.  It pulls 2.5 nodes per
 // node it advances, which is why larger boxes march instead.  The writers' words
 // of the brick plus two nodes on each side are staged in LDS, as are the aux
-// values; walls on any axis (WL): the ghost layer is computed in LDS from the
-// first layer, whose phase field two nodes around the brick the remaining lanes
-// pull with the writers' words read from memory.
+// values; z walls: the ghost layer is computed in LDS from the first layer, whose
+// phase field two nodes around the brick the remaining lanes pull with the
+// writers' words read from memory.
 constexpr int KX = 16, KY = 4, KZ = 4;
 constexpr int KOWN = KX * KY * KZ;
 constexpr int KHALO = (KX + 2) * (KY + 2) * (KZ + 2) - KOWN;
@@ -1469,18 +1469,12 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
         DC &C = case_at(a.cases, tl.x);
         const int x0 = tl.y, y0 = tl.z, z0 = tl.w;
         const int ax = min(KX, C.nx - x0), ay = min(KY, C.ny - y0), az = min(KZ, C.nz - z0);
-        // a coordinate beyond a wall (never wrapped); the others wrap
-        auto beyond = [&](int x, int y, int z) {
-            if (WL == WALLS_NONE) return false;
-            if (WL == WALLS_Z) return C.wall == 2 && (z < 0 || z >= C.nz);
-            return (C.wall == 0 && (x < 0 || x >= C.nx)) || (C.wall == 1 && (y < 0 || y >= C.ny)) ||
-                   (C.wall == 2 && (z < 0 || z >= C.nz));
-        };
+        const bool walls = WL == WALLS_Z && C.wall == 2;
+        auto beyond = [&](int z) { return walls && (z < 0 || z >= C.nz); };    // a wall's z does not wrap
         auto wrap = [](int v, int n) { return (v + 4 * n) % n; };       // v >= -2 >= -2 n
         // a ragged brick's upper halo falls on lanes of the full brick's own nodes
         const bool own = tid < KOWN && px < ax && py < ay && pz < az;
-        const bool pull = tid < KOWN + KHALO && px <= ax && py <= ay && pz <= az &&
-                          !beyond(x0 + px, y0 + py, z0 + pz);
+        const bool pull = tid < KOWN + KHALO && px <= ax && py <= ay && pz <= az && !beyond(z0 + pz);
         const Coord c = make_coord_xyz<WL>(C, wrap(x0 + px, C.nx), wrap(y0 + py, C.ny), wrap(z0 + pz, C.nz));
         FPull<ST, IN> v;
         if (pull) fpull_issue<ST, IN, CP_DEFAULT, true>(a, C, c, v);
@@ -1488,7 +1482,7 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
         // per lane; positions outside load node 0 and are not stored
         auto stage_at = [&](int e, bool &ok) {
             const int rx = e % KRX - 2, ry = (e / KRX) % KRY - 2, rz = e / KPL - 2;
-            ok = e < KREG && rx <= ax + 1 && ry <= ay + 1 && rz <= az + 1 && !beyond(x0 + rx, y0 + ry, z0 + rz);
+            ok = e < KREG && rx <= ax + 1 && ry <= ay + 1 && rz <= az + 1 && !beyond(z0 + rz);
             return (size_t)C.node_off +
                    (ok ? wrap(x0 + rx, C.nx) + C.nx * (wrap(y0 + ry, C.ny) + C.ny * wrap(z0 + rz, C.nz)) : 0);
         };
@@ -1535,29 +1529,16 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
             if (MV) wq[kidx(px, py, pz)] = qs;
         }
         if constexpr (WL != WALLS_NONE) {
-            // wall bricks: sides s0 .. s1 - 1 (0 low, 1 high) touch the brick;
-            // (b, w) of a position: in-plane coordinates and the wall coordinate
-            const int w = WL == WALLS_Z ? 2 : C.wall;
-            const int o0 = w == 0 ? x0 : (w == 1 ? y0 : z0), aw = w == 0 ? ax : (w == 1 ? ay : az);
-            const int nw = w == 0 ? C.nx : (w == 1 ? C.ny : C.nz);
-            const bool has = WL == WALLS_Z ? C.wall == 2 : C.wall >= 0;
-            const int s0 = has && o0 == 0 ? 0 : 1, s1 = has && o0 + aw == nw ? 2 : 1;
-            const int ab = w == 0 ? ay : ax, ac = w == 2 ? ay : az;      // in-plane extents
-            auto at = [&](int b, int cax, int layer, int &rx, int &ry, int &rz) {
-                rx = w == 0 ? layer : b;
-                ry = w == 0 ? b : (w == 1 ? layer : cax);
-                rz = w == 2 ? layer : cax;
-            };
+            // wall bricks: sides s0 .. s1 - 1 (0 low, 1 high) touch the brick
+            const int s0 = walls && z0 == 0 ? 0 : 1, s1 = walls && z0 + az == C.nz ? 2 : 1;
             if (s0 < s1) {
-                const int n = 2 * (ab + 4) + 2 * (ac + 2);               // the ring at distance 2
+                const int n = 2 * (ax + 4) + 2 * (ay + 2);               // the ring at distance 2
                 for (int q = tid - (KOWN + KHALO); q < n * (s1 - s0); q += KNT - (KOWN + KHALO)) {
                     if (q < 0) break;
-                    const int k = q >= n;
-                    int b, cax, rx, ry, rz;
-                    ring2_pos(q - k * n, ab, ac, b, cax);
-                    at(b, cax, (s0 + k ? nw - 1 : 0) - o0, rx, ry, rz);
-                    const Coord ch = make_coord_xyz<WL>(C, wrap(x0 + rx, C.nx), wrap(y0 + ry, C.ny),
-                                                        wrap(z0 + rz, C.nz));
+                    const int k = q >= n, rz = (s0 + k ? C.nz - 1 : 0) - z0;
+                    int rx, ry;
+                    ring2_pos(q - k * n, ax, ay, rx, ry);
+                    const Coord ch = make_coord_xyz<WL>(C, wrap(x0 + rx, C.nx), wrap(y0 + ry, C.ny), z0 + rz);
                     NodeState hs;
                     if constexpr (IN == LV_COMPACT) pull_node_c<ST, MV>(a, C, ch, hs);
                     else pull_node<ST, MV, CP_DEFAULT>(a, C, ch, hs);
@@ -1566,13 +1547,10 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
                     if (MV) wq[kidx(rx, ry, rz)] = qs;
                 }
                 __syncthreads();
-                const int wb = ab + 2, ng = wb * (ac + 2);
-                const int sb = w == 0 ? KRX : 1, scx = w == 2 ? KRX : KPL, sw = w == 0 ? 1 : (w == 1 ? KRX : KPL);
+                const int wb = ax + 2, ng = wb * (ay + 2);
                 for (int q = tid; q < ng * (s1 - s0); q += KNT) {
                     const int side = s0 + (q >= ng), r = q >= ng ? q - ng : q;
-                    int rx, ry, rz;
-                    at(r % wb - 1, r / wb - 1, (side ? nw - 1 : 0) - o0, rx, ry, rz);
-                    const int i = kidx(rx, ry, rz);
+                    const int i = kidx(r % wb - 1, r / wb - 1, (side ? C.nz - 1 : 0) - z0);
                     float gb = 0.f, gc = 0.f;
                     #pragma unroll
                     for (int db = -1; db <= 1; ++db) {
@@ -1580,7 +1558,7 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
                         for (int dc = -1; dc <= 1; ++dc) {
                             if (db == 0 && dc == 0) continue;
                             const float wgt = (db != 0 && dc != 0) ? (1.0f / 12.0f) : (1.0f / 3.0f);
-                            const float u = aux[i + db * sb + dc * scx].x;
+                            const float u = aux[i + db + dc * KRX].x;
                             gb += wgt * (float)db * u;
                             gc += wgt * (float)dc * u;
                         }
@@ -1588,7 +1566,7 @@ __global__ __launch_bounds__(KNT) void k_brick(FusedArgs fa)
                     const float4 f = aux[i];
                     const float gpar = sqrtf(gb * gb + gc * gc);
                     const float qw = MV && C.moving ? 2.0f * wq[i] : 0.f;
-                    aux[side ? i + sw : i - sw] =
+                    aux[side ? i + KPL : i - KPL] =
                         make_float4(f.x + C.cot[side] * gpar, qw * C.uw[side][0] - f.y, qw * C.uw[side][1] - f.z,
                                     qw * C.uw[side][2] - f.w);
                 }

@@ -77,7 +77,7 @@ struct lbcg_handle {
     int64_t launches[4] = {0, 0, 0, 0};
     // fused single-pass step
     bool fused = false;
-    bool brick = false;                // small boxes: k_brick instead of k_fused or the two-pass kernels
+    bool brick = false;                // small boxes: the single pass is k_brick's
     int zc = 16;
     int4 *d_ftiles = nullptr;
     int nftiles = 0;
@@ -329,13 +329,6 @@ template <int ST, int IN, int OUT>
 void launch_brick(lbcg_handle *h, hipStream_t st, const FusedArgs &fa, int grid)
 {
     const dim3 g(grid), b(KNT);
-    if constexpr (IN == LV_PAIR && OUT == LV_PAIR) {   // walls on x or y: pair levels only
-        if (h->walls == WALLS_ANY) {
-            if (h->moving) hipLaunchKernelGGL((k_brick<ST, true, WALLS_ANY, IN, OUT>), g, b, 0, st, fa);
-            else hipLaunchKernelGGL((k_brick<ST, false, WALLS_ANY, IN, OUT>), g, b, 0, st, fa);
-            return;
-        }
-    }
     if (h->moving) hipLaunchKernelGGL((k_brick<ST, true, WALLS_Z, IN, OUT>), g, b, 0, st, fa);
     else if (h->walls == WALLS_Z) hipLaunchKernelGGL((k_brick<ST, false, WALLS_Z, IN, OUT>), g, b, 0, st, fa);
     else hipLaunchKernelGGL((k_brick<ST, false, WALLS_NONE, IN, OUT>), g, b, 0, st, fa);
@@ -365,7 +358,7 @@ template <int ST>
 int launch_step(lbcg_handle *h, hipStream_t st)
 {
     StepArgs a = args_for(h);
-    if (h->fused || h->brick) {
+    if (h->fused) {
         int rc = for_format_runs(h, [&](int fmt, int c0, int c1) {
             const int t0 = h->ftile_begin[c0];
             const int nt = h->ftile_begin[c1 - 1] + h->ftile_count[c1 - 1] - t0;
@@ -643,7 +636,7 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     if (!out) return fail(LBCG_EINVAL, "out is NULL");
     *out = nullptr;
     if (!cases || !init || n_cases < 1) return fail(LBCG_EINVAL, "cases/init NULL or n_cases < 1");
-    lbcg_options o = {LBCG_FP32, 0, 0, 0, LBCG_KERNEL_AUTO, 0, 0, 0};
+    lbcg_options o = {LBCG_FP32, 0, 256, 0, LBCG_KERNEL_AUTO, 0, 0, 0};
     if (opt) o = *opt;
     if (o.graph_steps < 0) return fail(LBCG_EINVAL, "graph_steps must be >= 0");
     if (o.kernel < LBCG_KERNEL_AUTO || o.kernel > LBCG_KERNEL_FUSED) return fail(LBCG_EINVAL, "unknown kernel");
@@ -651,7 +644,6 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
     if (o.level < LBCG_LEVEL_AUTO || o.level > LBCG_LEVEL_COMPACT) return fail(LBCG_EINVAL, "unknown level format");
     if (o.storage != LBCG_FP32 && o.storage != LBCG_FP16S && o.storage != LBCG_BF16S)
         return fail(LBCG_EINVAL, "unknown storage format");
-    const int opt_block = o.block_nodes;
     if (o.block_nodes == 0) o.block_nodes = 256;
     if (o.block_nodes < 64 || o.block_nodes > 256 || o.block_nodes % 64)
         return fail(LBCG_EINVAL, "block_nodes must be 64, 128, 192 or 256");
@@ -748,25 +740,17 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
             n += (int64_t)((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty) * ((d.nz + tz - 1) / tz);
         return n;
     };
-    // Small boxes take the brick kernel where the caller left the launch shape
-    // open: up to two bricks per CU.  A round of bricks takes about 10 us
-    // whatever the box, a marching tile 3 + 5 (zc + 2) us at its best chunk
-    // below, and the two-pass step 13 us plus its bandwidth.  Measured, FP32 us
-    // per step, brick / marching (best chunk) / two-pass: 32^3 (128 bricks)
-    // 12.0 / 19.8 / 13.9, 32 x 32 x 128 (512) 21.1 / 24.4 / 19.3, 48^3 (432)
-    // 23.5 / 29.0 / 19.0, 64^3 (1024) 43.0 / 32.3 / 34.0; FP16S at 48^3 23.0 /
-    // 24.6, at 64^3 41.9 / 28.5.  A handle that has to take the two-pass step
-    // (walls on x or y, pair levels) saves two launches with one brick per CU
-    // (plates on 64 x 64 x 4 nodes 15.4 us in passes, 12 in bricks; beyond it 42 x
-    // 69 x 20, 270 bricks, 17.9 against 25.5, plates on 140 x 140 x 4, 315 bricks, 21.9
-    // against 22.6), in FP32: in the 16-bit forms the passes' last-bit rounding
-    // would change the stored values.
-    const int64_t bricks = ntiles_of(KX, KY, KZ);
-    const bool single = h->fused && bricks <= 2 * (int64_t)ncu;
-    const bool instead = !h->fused && o.kernel == LBCG_KERNEL_AUTO && opt_block == 0 && o.persistent_blocks == 0 &&
-                         o.storage == LBCG_FP32 && bricks <= (int64_t)ncu;
-    h->brick = dev_ok && o.zchunk == 0 && (single || instead) && h->one_rsrc[h->level] &&
-               (h->level == LV_PAIR || o.storage == LBCG_FP32);
+    // Small boxes of the fused step take the brick kernel where the caller left
+    // the chunk open: up to two bricks per CU.  A round of bricks takes about 10 us
+    // whatever the box, a marching tile 3 + 5 (zc + 2) us at its best chunk below.
+    // Measured, FP32 us per step, brick / marching (best chunk): 32^3 (128 bricks)
+    // 12.0 / 19.8, 32 x 32 x 128 (512) 21.1 / 24.4, 48^3 (432) 23.5 / 29.0, 64^3 (1024)
+    // 43.0 / 32.3; FP16S at 48^3 23.0 / 24.6, at 64^3 41.9 / 28.5.  (The two-pass step
+    // takes 13.9, 19.3, 19.0 and 34.0 us on those boxes in FP32, less than two rounds of
+    // bricks, but rounds differently from the fused step that these handles have
+    // always taken; for the same reason walls on x or y keep the two-pass step.)
+    h->brick = h->fused && dev_ok && o.zchunk == 0 && ntiles_of(KX, KY, KZ) <= 2 * (int64_t)ncu &&
+               h->one_rsrc[h->level] && (h->level == LV_PAIR || o.storage == LBCG_FP32);
     h->zc = o.zchunk;
     if (h->brick) {
         h->zc = KZ;
@@ -809,7 +793,7 @@ int lbcg_init(const lbcg_case *cases, int32_t n_cases, const lbcg_fields *init, 
         h->ftile_begin.push_back((int)ftiles.size());
         const DevCase &d = h->dc[c];
         const int sx = h->brick ? KX : FTX, sy = h->brick ? KY : FTY;
-        if (h->fused || h->brick)
+        if (h->fused)
             for (int z0 = 0; z0 < d.nz; z0 += h->zc)
                 for (int y0 = 0; y0 < d.ny; y0 += sy)
                     for (int x0 = 0; x0 < d.nx; x0 += sx) ftiles.push_back(make_int4(c, x0, y0, z0));
