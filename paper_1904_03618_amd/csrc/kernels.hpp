@@ -1318,8 +1318,11 @@ __device__ inline void stencil_lds(float4 (*ring)[FREG], int z, int tx, int ty, 
 // SO: levels read through one buffer resource per case (the host takes it
 // where every case's level is below 2^31 bytes).
 // CPS: cache policy of the stored level (lbcg_init chooses by its size).
+// Workgroups per CU: three for 16-bit pairs at rest; their instance with moving
+// walls needs 194 registers, and at the 168 of three workgroups it spilled 22
+// (128^3, FP16S us per step: 167 with three, 125 with two).
 template <int ST, bool MV, int WL, int IN, int OUT, bool SO, int CPS>
-__global__ __launch_bounds__(FNT, ST != LBCG_FP32 && IN == LV_PAIR ? 3 : 2) void k_fused(FusedArgs fa)
+__global__ __launch_bounds__(FNT, ST != LBCG_FP32 && IN == LV_PAIR && !MV ? 3 : 2) void k_fused(FusedArgs fa)
 {
     __shared__ float4 ring[FSLOTS][FREG];
     __shared__ float2 rring[4][RREG];

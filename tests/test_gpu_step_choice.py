@@ -86,3 +86,20 @@ def test_small_boxes_of_the_fused_step_run_bricks(name):
         assert _run([case], **opt)[1:4] == ("fused", 4, {"fused"}), opt
     assert _run([case], zchunk=3)[1:4] == ("fused", 3, {"fused"})
     assert _run([case], kernel="twopass")[1:3] == ("twopass", 0)
+
+
+@pytest.mark.parametrize("storage", ["fp16s", "bf16s"])
+def test_moving_walls_in_16_bits_march_two_workgroups_per_cu(storage):
+    """The moving-wall instance of 16-bit pairs holds two workgroups per CU in
+    its registers (three made it spill): the default chunk is the rule's for two."""
+    import torch
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    case = _moving(W.random_state_case(128, 64, 128, seed=90, bc=(0, 0, 1)), ((0.02, 0.01, 0.0), (0.0, -0.01, 0.0)))
+    tiles = lambda zc: 4 * 8 * -(-128 // zc)
+    assert tiles(64) < 2 * slots
+    best = min(range(1, 65), key=lambda zc: (-(-tiles(zc) // slots) * (zc + 2), -zc))
+    h = B.lbcg_init([case], storage=storage)
+    try:
+        assert (B.lbcg_step_kernel(h), B.lbcg_zchunk(h)) == ("fused", best)
+    finally:
+        B.lbcg_free(h)
