@@ -242,8 +242,11 @@ __device__ inline f32x4 bias4(const float *bias, int oc0, const sg_view &y, cons
     return b;
 }
 
+// Three workgroups per CU for two output blocks of 16-channel chunks: left to
+// itself the compiler took 173 registers, five too many for three (16 -> 32
+// channels on 128^3 positions 93 us, 79 so; no spills).
 template <int NO, int BZ, int CT, bool DYR, bool WLDS>
-__global__ __launch_bounds__(256) void k_conv3(sg_view x, const bf16 *__restrict__ W, const float *__restrict__ bias,
+__global__ __launch_bounds__(256, NO == 2 && BZ == 8 && CT == 16 ? 3 : 1) void k_conv3(sg_view x, const bf16 *__restrict__ W, const float *__restrict__ bias,
                                                int pmask, int relu, sg_view y, sg_view y32, int accumulate, int nbx,
                                                int nby, int nbz)
 {
