@@ -5,9 +5,9 @@ configuration (step kernel, workgroup tile, persistent grid, z-chunk, graph
 capture) on a scratch handle built from a sample of the cases, and returns the
 fastest as keyword options for ``lbcg_init``.  Results are cached in a JSON
 file in the user's cache directory (``LBCG_AUTOTUNE_CACHE`` overrides it),
-keyed by the box-size class of the cases and the storage format, so a later
-run on the same machine with the same kind of workload reuses the choice
-without timing; ``cache=None`` times every call.
+keyed by the box-size class of the cases, the storage format and the version
+of the step kernels, so a later run on the same machine with the same kind of
+workload reuses the choice without timing; ``cache=None`` times every call.
 """
 from __future__ import annotations
 
@@ -17,30 +17,36 @@ import os
 DEFAULT_CACHE = os.environ.get("LBCG_AUTOTUNE_CACHE",
                                os.path.join(os.path.expanduser("~"), ".cache", "lbcg", "autotune.json"))
 
+# Part of the cache key: raised when the step kernels or the candidates change, so
+# that a choice made among others is not reused.
+VERSION = 2
+
 
 def _moving(p):
     return any(v != 0.0 for side in p.get("wall_u", ()) for v in side)
 
 
 def box_class(cases, storage):
-    """Cache key: storage, number of cases, wall/periodic mix, the node count
-    rounded to two significant digits, and the number of cases with moving
+    """Cache key: version, storage, number of cases, wall/periodic mix, the node
+    count rounded to two significant digits, and the number of cases with moving
     walls when there are any (those run another instantiation of the step
     kernels)."""
     n = sum(int(p["nx"]) * int(p["ny"]) * int(p["nz"]) for p, _ in cases)
     walls = sum(1 for p, _ in cases if any(p["bc"]))
     lo = min(min(p["nx"], p["ny"], p["nz"]) for p, _ in cases)
     hi = max(max(p["nx"], p["ny"], p["nz"]) for p, _ in cases)
-    key = f"{storage}|cases={len(cases)}|walls={walls}|side={lo}-{hi}|nodes={float(f'{n:.2g}'):.3g}"
+    key = f"v{VERSION}|{storage}|cases={len(cases)}|walls={walls}|side={lo}-{hi}|nodes={float(f'{n:.2g}'):.3g}"
     moving = sum(1 for p, _ in cases if _moving(p))
     return key + (f"|moving={moving}" if moving else "")
 
 
-def candidates(eligible_fused):
+def candidates(eligible_fused, whole=True):
     """Launch shapes to time: the two-pass step (256- or 128-node tiles,
     with or without a persistent grid) and, where the cases allow it, the
-    fused step at 16-, 32- and 64-plane chunks; each with and without an
-    8-step graph."""
+    fused step at 16-, 32- and 64-plane chunks and at its default (zchunk 0:
+    bricks for small boxes, else the chunk that fills the GPU; only where the
+    timed cases are the whole batch, since it depends on all of them); each with
+    and without an 8-step graph."""
     out = []
     for block in (256, 128):
         for persistent in (0, 1024):
@@ -48,7 +54,7 @@ def candidates(eligible_fused):
                 out.append(dict(kernel="twopass", block_nodes=block, persistent_blocks=persistent,
                                 graph_steps=graph))
     if eligible_fused:
-        for zc in (16, 32, 64):
+        for zc in ((0,) if whole else ()) + (16, 32, 64):
             for graph in (0, 8):
                 out.append(dict(kernel="fused", zchunk=zc, persistent_blocks=0, graph_steps=graph))
     return out
@@ -92,7 +98,7 @@ def autotune(cases, storage="fp16s", sample_every=8, steps=24, warmup=8, cache=D
     sample = cases[::sample_every] if len(cases) >= 8 * sample_every else cases
     nodes = sum(int(p["nx"]) * int(p["ny"]) * int(p["nz"]) for p, _ in sample)
     results = []
-    for opts in candidates(_fused_ok(cases)):
+    for opts in candidates(_fused_ok(cases), whole=len(sample) == len(cases)):
         ms = time_config(B, sample, storage, opts, steps=steps, warmup=warmup)
         results.append({"options": opts, "ms_per_step": ms, "MLUPS": nodes / ms / 1e3})
         if log:
