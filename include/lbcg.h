@@ -240,9 +240,10 @@ int lbcg_get_populations(lbcg_handle *h, int32_t case_id, float *f);
  * recording an event pair around every kernel of every following step
  * (enable = 0 stops).  lbcg_timing_read synchronises the stream and writes,
  * for the kernels {moments pass, wall ghost layer, collision pass, fused
- * step} (a handle on the fused step records only the last), the summed duration in milliseconds into ms[4] and the number of
- * recorded launches into launches[4]; it then clears the totals.  Errors: LBCG_ESTATE,
- * LBCG_EINVAL (NULL output), LBCG_EDEVICE. */
+ * step} (a handle on the fused step records only the last), the summed
+ * duration in milliseconds into ms[4] and the number of recorded launches into
+ * launches[4]; it then clears the totals.  Errors: LBCG_ESTATE, LBCG_EINVAL
+ * (NULL output), LBCG_EDEVICE. */
 int lbcg_timing(lbcg_handle *h, int32_t enable);
 int lbcg_timing_read(lbcg_handle *h, double *ms, int64_t *launches);
 
@@ -269,7 +270,9 @@ int32_t lbcg_zchunk(const lbcg_handle *h);
  * case shapes, in the same case order, and storage format (the image records
  * every case's extents and array offsets and the load compares them;
  * parameters other than the shapes are the handle's own); the next steps then
- * continue bit for bit as the saved handle would have.  Errors: LBCG_ESTATE,
+ * continue bit for bit as the saved handle would have, if this one runs the same
+ * step kernel (lbcg_step_kernel; with moving z walls also the same form of it,
+ * bricks or marching tiles, which round apart there).  Errors: LBCG_ESTATE,
  * LBCG_EINVAL (NULL buffer, too small, or an image of other case extents,
  * case order, storage or level format), LBCG_EDEVICE. */
 int64_t lbcg_checkpoint_bytes(const lbcg_handle *h);

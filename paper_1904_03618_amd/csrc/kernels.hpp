@@ -293,7 +293,7 @@ __device__ inline void pull_issue(const StepArgs &a, DC &C, const Coord &c, type
 }
 
 // Decode phase: deviations plus the writers' densities from the LDS plane
-// ring (as pull_one does with the densities from memory).
+// ring (as pull_all does with the densities from memory).
 template <int ST, bool MV, int ROW = RW, int I = 0>
 __device__ inline void pull_decode(const StepArgs &a, DC &C, const Coord &c, const float2 own,
                                    const float2 *const (&rl)[3], int ri, const typename Storage<ST>::P (&v)[Q],

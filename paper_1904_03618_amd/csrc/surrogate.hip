@@ -175,9 +175,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(sg_view x, const bf16 *__restr
 // (dz, dx, channel group) combinations, each block's three dy taps in turn; a
 // lane then loads the 6 halo rows its 4 output rows need once and feeds them to
 // three K blocks, half the LDS reads.  false: K blocks of four consecutive (tap,
-// channel group) pairs.  The order of a layer is fixed by its channels and
-// extents (sg_conv3d_fwd): networks reproduce their activations bit for bit
-// whatever brick or launch shape runs the layer.
+// channel group) pairs.  sg_conv3d_fwd chooses chunk length and order.
 // WLDS: the chunk's weights are staged in LDS too, and the next chunk's loads
 // fly during the K loop.  For launches that leave CUs idle or with one workgroup:
 // there every K block would otherwise wait for its weights from L2.
@@ -1486,10 +1484,13 @@ int sg_conv3d_fwd(const sg_view *x, const void *w, const float *bias, int32_t co
                      (hipStream_t)hip_stream};
     const bool bricks = x->w % 16 == 0 && x->h % 4 == 0 && x->d % 4 == 0;
     if (k == 3 && bricks && (int64_t)x->d * x->h * x->w * (x->ctot / 8) < (int64_t)1 << 31) {
-        // Summation order (chunk length, DYR) by channels and extents alone; the
-        // launch shape within it by size.  Chunks: 16 channels where ci is no
-        // multiple of 32 and two planes per wave fit, or where ci leaves 24 (an
-        // 8-channel layer's one chunk is 8 long); else 32.
+        // The order of a layer's sums (chunk length, DYR) follows from its channels
+        // and extents, save that layers of a multiple of 32 outputs leave DYR at the
+        // size `big` below, which counts the batch: a 32 -> 32 layer on 64 x 64 x 32
+        // positions sums in another order for one item than for two.  Within an
+        // order the launch shape goes by size and changes no bit.  Chunks: 16
+        // channels where ci is no multiple of 32 and two planes per wave fit, or
+        // where ci leaves 24 (an 8-channel layer's one chunk is 8 long); else 32.
         const bool two = x->d % 8 == 0, few = x->c % 32 != 0 && two, odd = x->c % 32 == 24;
         // large: two planes per wave for 32-channel chunks when that still leaves
         // at least 512 workgroups (less halo per output)
