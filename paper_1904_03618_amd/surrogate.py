@@ -290,14 +290,18 @@ class UNet:
         (pickle gives every tensor memory of its own, as does `layer.w.data = t`)."""
         if not self.flat.is_contiguous():
             return False
-        base, at = [f.data_ptr() for f in self.flat], 0
+        p, row = self.flat.data_ptr(), 4 * self.flat.shape[1]
+        end = p + row
         for l in self.layers:
-            for (w, g, m, v), n in zip(l.params(), (l.co * l.K, l.co)):
-                if any(t.data_ptr() != p + 4 * at or t.numel() != n for t, p in zip((w, g, m, v), base)):
-                    return False
-                at += n
-            at += l.co_pad - l.co
-        return at == self.flat.shape[1]
+            n = l.co * l.K
+            q = p + 4 * n
+            if (l.w.numel() != n or l.b.numel() != l.co or l.w.data_ptr() != p or l.b.data_ptr() != q or
+                    l.gw.data_ptr() != p + row or l.gb.data_ptr() != q + row or
+                    l.mw.data_ptr() != p + 2 * row or l.mb.data_ptr() != q + 2 * row or
+                    l.vw.data_ptr() != p + 3 * row or l.vb.data_ptr() != q + 3 * row):
+                return False
+            p = q + 4 * l.co_pad
+        return p == end
 
     def adam(self, lr, b1=0.9, b2=0.999, eps=1e-8):
         self.step_count += 1
