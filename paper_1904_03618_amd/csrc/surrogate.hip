@@ -397,10 +397,10 @@ __global__ __launch_bounds__(256, NO == 2 && BZ == 8 && CT == 16 ? 3 : 1) void k
             };
             // register sets in turn, so a plane's MFMAs never wait for the fetch
             // issued after them; the fetch past the end re-reads a valid block.
-            // 16-channel chunks fetch their weights at use: the registers saved
-            // let one more workgroup stay on the CU, which hides more (16 -> 16
-            // channels on the 128 x 128 x 512 box 266 -> 254 us).
-            constexpr bool AHEAD = CT != 16;
+            // 8- and 16-channel chunks fetch their weights at use: the registers
+            // saved let one more workgroup stay on the CU, which hides more (on the
+            // 128 x 128 x 512 box 16 -> 16 channels 266 -> 254 us, 8 -> 16 177 -> 166).
+            constexpr bool AHEAD = CT == 32;
             bf16x8 R0[NR], R1[NR], A0[3][NO], A1[3][NO];
             auto step = [&](int s, bf16x8 (&Rc)[NR], bf16x8 (&Rn)[NR], bf16x8 (&Ac)[3][NO], bf16x8 (&An)[3][NO]) {
                 const int sn = min(s + 1, nsb - 1);
