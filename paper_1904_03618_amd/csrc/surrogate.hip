@@ -1498,8 +1498,12 @@ int sg_conv3d_fwd(const sg_view *x, const void *w, const float *bias, int32_t co
         // Below two workgroups of one output block per CU the weights go through
         // LDS: 192 -> 64 channels on 4 x 16^3 60 -> 26 us, 64 -> 64 there 22.7 ->
         // 12.7; above it the larger LDS use costs more (32 -> 64 on 128 x 32 x 32 25
-        // us without, 43 with).
-        const bool small = P / 256 * (co / 16) <= 512;
+        // us without, 43 with).  Not for the few input channels whose K loop is over
+        // before the staging has paid (kernel us on 12 x 64 x 64, with / without: 8 ->
+        // 16 7.7 / 5.7, 48 -> 16 11.3 / 9.8, 128 -> 16 17.3 / 19.9; 16 -> 32 9.9 / 8.8;
+        // on 4 x 16^3 32 -> 32 8.8 / 10.2): up to 48 with one output block per
+        // workgroup, up to 16 where the other form takes two.
+        const bool small = P / 256 * (co / 16) <= 512 && x->c > (co % 32 ? 48 : 16);
         if (co % 32 == 0 && (few || odd)) {
             if (few) launch_conv3<2, 8, 16, false, false>(a);
             else launch_conv3<2, 4, 16, false, false>(a);

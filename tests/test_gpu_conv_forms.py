@@ -57,6 +57,24 @@ def test_whole_brick_layers(shape, ci, co, pmask):
     assert ok, err
 
 
+# both sides of the rule that sends a small layer's weights through LDS (more than
+# 48 input channels with one output block per workgroup, more than 16 with two)
+@pytest.mark.parametrize("shape", [(1, 4, 4, 16), (2, 12, 8, 32)])
+@pytest.mark.parametrize("ci,co", [(8, 16), (48, 16), (56, 16), (64, 48), (16, 32), (32, 32), (40, 64)])
+def test_small_whole_brick_layers(shape, ci, co):
+    import torch
+    from oracle import conv_ref as R
+    from paper_1904_03618_amd import surrogate as S
+    rng = np.random.default_rng([*shape, ci, co])
+    layer, W64, b64 = _layer(ci, co, rng)
+    xt, x64 = bft(rng.standard_normal(shape + (ci,)))
+    for pmask in (3, 4):
+        y32 = torch.full(shape + (co,), np.nan, device="cuda")
+        layer.fwd(S.view(xt), None, S.view(y32), pmask=pmask)
+        ok, err = close(y32.cpu().numpy(), R.conv3d(x64, W64, b64, k=3, pmask=pmask))
+        assert ok, (pmask, err)
+
+
 @pytest.mark.parametrize("co", [16, 32])
 def test_inputs_of_two_gigabytes(co):
     """2^31 bytes of input on ragged extents: past the 32-bit byte offsets of the
