@@ -288,9 +288,10 @@ class UNet:
         """Whether the layers' arrays still fill self.flat as __init__ placed them.
         By address: a tensor object can outlive its place in the flat arrays
         (pickle gives every tensor memory of its own, as does `layer.w.data = t`)."""
-        if not self.flat.is_contiguous():
+        flat = getattr(self, "flat", None)            # (networks pickled before it have none)
+        if flat is None or not flat.is_contiguous():
             return False
-        p, row = self.flat.data_ptr(), 4 * self.flat.shape[1]
+        p, row = flat.data_ptr(), 4 * flat.shape[1]
         end = p + row
         for l in self.layers:
             n = l.co * l.K

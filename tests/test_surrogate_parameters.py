@@ -60,6 +60,15 @@ def _replaced(n):
     return n
 
 
+def _before_flat(n):
+    """As a network pickled before its arrays were flat: every layer its own."""
+    del n.flat
+    for l in n.layers:
+        for k in ("w", "b", "gw", "gb", "mw", "mb", "vw", "vb", "bias_pad"):
+            setattr(l, k, getattr(l, k).clone())
+    return n
+
+
 def _without_fake(n, f):
     fake = n.__dict__.pop("fake")
     out = f(n)
@@ -73,6 +82,7 @@ FORMS = {
     "pickled": (lambda n: _without_fake(n, lambda m: pickle.loads(pickle.dumps(m))), 30),
     "tensor data replaced": (_own_storage, 30),
     "attributes replaced": (_replaced, 30),
+    "without flat arrays": (_before_flat, 30),
     "a layer left out": (lambda n: (n.layers.pop(3), n)[1], 28),
 }
 
