@@ -1529,11 +1529,13 @@ int sg_conv3d_fwd(const sg_view *x, const void *w, const float *bias, int32_t co
     // 32-bit byte offsets: tensors and weights below 2^31 bytes
     if (P * x->ctot * 2 < (int64_t)1 << 31 && (int64_t)co * k * k * k * x->c * 2 < (int64_t)1 << 31) {
         const int64_t waves = P / 64 * (co / 16);         // at 64 positions and one output block each
-        // two waves per SIMD at 64 positions each keep the reuse of four fragments
-        // per weight fragment; below that 16 positions per wave fill the GPU
-        // (16 -> 16 on 72 x 40 x 40, 1800 waves: 17.6 us, 27 with 16; 64 -> 128 on 4
-        // x 8^3, 256 waves: 21.5, 40 with 64)
-        if (waves >= 2048 && co % 32 == 0) launch_direct<2, 4, 2>(a, k);
+        // 64 positions per wave keep the reuse of four fragments per weight fragment
+        // while there are waves enough; below that 16 positions per wave fill the
+        // GPU (16 -> 16 on 72 x 40 x 40, 1800 waves: 17.6 us, 27 with 16; 64 -> 128 on
+        // 4 x 8^3, 256 waves: 21.5, 40 with 64).  Two output blocks per wave once one
+        // each would put a second wave on some of the 1024 SIMDs (192 -> 64 on 30 x 31
+        // x 33, 1916 waves: 186 us with one, 117 with two; at 928 waves 99 with one).
+        if (waves >= 1024 && co % 32 == 0) launch_direct<2, 4, 2>(a, k);
         else if (waves >= 512) launch_direct<1, 4, 3>(a, k);
         else launch_direct<1, 1, 8>(a, k);
         return status();

@@ -122,3 +122,20 @@ def test_mse_over_more_positions_than_lanes(ctot, coff):
     f64 = lambda t: t[..., coff:coff + 4].double().cpu().numpy()
     l64, g64 = R.mse(f64(out), f64(tgt))
     assert abs(loss[0].item() - l64) < 1e-6 * l64 and close(f64(grad), g64, 1e-6)[0]
+
+
+# ragged layers of 32 outputs per workgroup on both sides of 1024 waves of one block
+@pytest.mark.parametrize("shape,ci,co", [((1, 7, 33, 67), 24, 64), ((1, 9, 35, 53), 24, 64), ((2, 17, 19, 23), 16, 128)])
+def test_ragged_layers_around_a_wave_per_simd(shape, ci, co):
+    import torch
+    from oracle import conv_ref as R
+    from paper_1904_03618_amd import surrogate as S
+    n, d, h, w = shape
+    assert (n * d * h * w // 64 * (co // 16) >= 1024) == (shape != (1, 7, 33, 67))
+    rng = np.random.default_rng([*shape, ci, co])
+    layer, W64, b64 = _layer(ci, co, rng)
+    xt, x64 = bft(rng.standard_normal(shape + (ci,)))
+    y32 = torch.full(shape + (co,), np.nan, device="cuda")
+    layer.fwd(S.view(xt), None, S.view(y32), pmask=3)
+    ok, err = close(y32.cpu().numpy(), R.conv3d(x64, W64, b64, k=3, pmask=3))
+    assert ok, err
